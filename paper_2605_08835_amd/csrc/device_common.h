@@ -81,12 +81,13 @@ __device__ inline bf16x8 buf_load16(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
 
-// One 16-byte-per-lane direct-to-LDS load (64 lanes -> 1 KB at `lds`).
+// One 16-byte-per-lane direct-to-LDS load (64 lanes -> 1 KB at `lds`) from
+// byte off (per lane) + soff (uniform) of the resource.
 // The builtin exists only for the device pass; the host pass of this file
 // compiles the kernels' launch stubs and never runs this body.
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, bf16* lds, int off) {
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, bf16* lds, int off, int soff) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, off, 0, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, off, soff, 0, 0);
 #endif
 }
 

@@ -391,76 +391,6 @@ __device__ __forceinline__ void epilogue_staged(const GemmArgs& a, const f32x16 
   });
 }
 
-// Epilogue of the large wave tiles (128 x 128 per wave, accumulators in
-// AGPRs): each 32-row group of the wave is first written raw (fp32) into a
-// wave-private LDS slab, then finished from there in row-contiguous runs of
-// 8 outputs per lane (bias, time bias, residual), with the same arithmetic
-// as the other epilogues.  Reading the accumulators only to copy them keeps
-// the register demand low (the register-staged epilogue spilled here).
-// The host sends only layers without GEGLU, a row scale, query columns, a
-// transposed part or an fp32 output.
-template <int WC>
-constexpr int SLAB_LD = WC + 4;  // floats per slab row
-
-template <int BM, int BN, int WM, int WN, int TM, int TN>
-__device__ __forceinline__ void epilogue_slab(const GemmArgs& a, const f32x16 (&acc)[TM][TN], int m0, int n0,
-                                              int wm, int wn, int lane, float* R) {
-  constexpr int WC = BN / WN;
-  constexpr int LD = SLAB_LD<WC>;
-  constexpr int CP = WC / 8, NCH = 32 * CP / 64;  // 8-output chunks per row; per lane
-  static_assert((32 * CP) % 64 == 0, "row chunks spread evenly over the lanes");
-  const Epi& e = a.epi;
-  const int lr = lane & 31, hq = 4 * (lane >> 5);
-  const int nc0 = n0 + wn * WC;  // first column of the wave
-  const bf16* resid = reinterpret_cast<const bf16*>(e.resid);
-  static_for<0, TM>([&](auto I) {
-    const int mrow0 = m0 + wm * (BM / WM) + I.value * 32;
-    static_for<0, TN>([&](auto J) {
-      const f32x16 v = acc[I.value][J.value];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(R + lr * LD + J.value * 32 + 8 * q + hq) =
-            make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    });
-    asm volatile("" ::: "memory");  // (one wave's LDS accesses complete in order)
-    bf16x8 rr[NCH];
-    if (resid) {
-#pragma unroll
-      for (int u = 0; u < NCH; ++u) {
-        const int c = lane + 64 * u, row = c / CP, ch = c - row * CP, m = mrow0 + row;
-        bf16x8 r = {};
-        if (m < a.M) r = *reinterpret_cast<const bf16x8*>(resid + (long)m * e.ldr + nc0 + ch * 8);
-        rr[u] = r;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < NCH; ++u) {
-      const int c = lane + 64 * u, row = c / CP, ch = c - row * CP, m = mrow0 + row;
-      const int n = nc0 + 8 * ch;
-      const float* src = R + row * LD + 8 * ch;
-      // (one rounding for the bias: fmaf with scale 1, as in the other epilogues)
-      float x[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = fmaf(src[k], 1.0f, e.bias ? e.bias[n + k] : 0.f);
-      if (e.tbias && m < a.M) {
-        const float* tb = e.tbias + (long)(m / e.hw) * e.tb_ld + e.tb_off + n;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] += tb[k];
-      }
-      if (resid) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] += (float)rr[u][k];
-      }
-      bf16x8 o;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) o[k] = (bf16)x[k];
-      if (m < a.M)
-        *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(e.out) + out_row(e, m) * e.ldo + n) = o;
-    }
-    asm volatile("" ::: "memory");
-  });
-}
-
 // The transposed part of a QKV projection (V written [image][channel][token]
 // for the attention kernel): the wave stages its 32 tokens x WC channels
 // channel-major, then stores 16-byte runs of 8 consecutive tokens.  Needs
@@ -704,19 +634,25 @@ __global__ __launch_bounds__(256, MINB) void gemm_bf16_kernel(GemmArgs a) {
   epilogue_tiles<BM, BN, WM, WN>(a, acc, m0, n0, wm, wn, lane);
 }
 
-
-
-
 // ------------------------------------------------- bf16 MFMA, direct-to-LDS
-// Same tiles and C^T epilogue as above, for the uniform-tap loader modes
-// (1, 2), with the operand tiles fetched by buffer_load ... lds: each 64-lane
-// load writes 1 KB of LDS contiguously (lane l at byte 16 l), so the loads
-// need no registers and three K stages stay in flight.  A tile row holds the
-// four 16-byte chunks of a 32-deep K slice; chunk c of row r sits in slot
-// c ^ ((r >> 2) & 3), which keeps the fragment reads of 8 consecutive rows
-// on distinct banks.  Lane l of a load writes (row 16 i + l / 4, slot l % 4)
-// and therefore fetches chunk (l % 4) ^ ((row >> 2) & 3) from global memory.
-constexpr int DKS = 32;  // K depth per stage (the split-K and loader-mode granule)
+// The C^T tiles of the uniform-tap loader modes (1, 2), with the operand tiles
+// fetched by buffer_load ... lds: each 64-lane load writes 1 KB of LDS
+// contiguously (lane l at byte 16 l), so the loads need no registers.  A tile
+// row holds the CPR = DK / 8 16-byte chunks of a DK-deep K slice; chunk c of
+// row r sits in slot c ^ swz(r), which keeps the fragment reads of 16
+// consecutive rows on distinct banks.  Lane l of a load writes (row
+// (64 / CPR) i + l / CPR, slot l % CPR) and fetches the chunk of that slot.
+//
+// What bounds these kernels is the operand stream: without the loads the
+// products with their LDS reads run at 1500-1900 TFLOP/s, the loads alone take
+// 75-95 % of the kernel's time.  A row of 64 bytes (DK = 32) moves a whole
+// 128-byte line from L2 for half of it: 66 B/ns per CU against 130 for rows of
+// 128 bytes (DK = 64; a loop of such loads over 2.6 MB).  So every layer whose
+// channels are multiples of 64 takes 64-deep stages; DKS-deep ones serve the
+// rest (conv_in, padded to 32 channels).  Against 32-deep stages with the
+// addresses formed per tile: 196608 x 320 x 2880 458 -> 323 us, 12288 x 1280 x
+// 11520 (2 splits) 364 -> 331 us, 512 x 1280 x 5120 100 -> 25 us.
+constexpr int DKS = 32;  // the smallest stage depth (the granule of split K and of the loader modes)
 
 // Slot swizzle of a tile row's 16-byte chunks: the fragment reads of rows
 // r..r+15 at one logical chunk land on distinct 16-byte bank groups (4
@@ -726,191 +662,246 @@ __device__ __forceinline__ int swz(int r) {
   return CPR == 4 ? (r >> 2) & 3 : (r >> 1) & 7;
 }
 
-template <int BM, int BN, int WM, int WN, int MODE, int DNS, int MINB, int DK, bool TI>
+// Position of the operand loads in the K tiles, all wave-uniform.  Tiles come
+// in runs: with TI (images larger than 8x8) a run is one 32-channel block
+// under all taps of its layer, otherwise one tap (or 1x1 layer) over the
+// channels of one source.  Inside a run a tile only adds constants to the
+// source pointer, the weight offset and the tap number, so the refill beside
+// the products is a handful of scalar instructions plus two vector ones per
+// A load (the per-tile selects and divisions it replaces cost about 140
+// instructions, as long as the tile's products).
+struct KPos {
+  const char* ab;    // source + (tap displacement * channels + channel) elements
+  int boff;          // byte offset of the tile's weight columns
+  int sh;            // 31 - tap (0..8; 9 = every row masked)
+  int dead;          // bit 31: past the last tile
+  int left, tp;      // tiles until the next run; tap step within the run
+  int da, daw, db;   // per-tile steps: source bytes (daw where a kernel row ends), weight bytes
+  int dsh, dshw, wm; // tap steps likewise; wm: bit tp set where a kernel row ends
+  int togo;          // tiles until the end of this block's K range
+  int seg, cb, tap;  // of the run
+  int cs2;           // bytes per pixel of the run's source
+  bool ti;           // the run steps through taps
+};
+
+// A wave-uniform value the compiler would otherwise keep in vector registers
+// (what divisions and their users leave there).
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ const char* uni(const char* p) {
+  const uint64_t v = (uint64_t)p;
+  return (const char*)(((uint64_t)(uint32_t)uni((int)(v >> 32)) << 32) | (uint32_t)uni((int)v));
+}
+
+template <typename T>
+__device__ __forceinline__ T pick(bool c, T a, T b) {
+  return c ? a : b;
+}
+
+// A and B tiles of DK-deep K slices in DNS LDS stages, one barrier per tile.
+// All stages are in flight; fragments are read ahead of their products (a
+// 16-deep substep, or a tile for the smallest wave tiles), the next tile's
+// first ones after its wait and the barrier, beside this tile's last products,
+// and with them goes the refill of the stage this tile has freed.
+// UP: the layer upsamples its input (nearest 2x), so the input pixel of a tap
+// depends on the row's parity and is formed per tile.
+template <int BM, int BN, int WM, int WN, bool UP, int DK, int DNS, int MINB, bool TI>
 __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmArgs a) {
   constexpr int NWV = WM * WN;                          // waves per block
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int CPR = DK / 8, RPL = 64 / CPR;           // 16-byte chunks per row, rows per load
   constexpr int AI = BM / RPL, BI = BN / RPL;           // 1 KB loads per tile
-  constexpr int AW = AI / NWV, BW = (BI + NWV - 1) / NWV;  // ... per wave (B: some waves one fewer)
-  constexpr int LPT_MIN = AW + BI / NWV;                // loads per tile of the lightest wave
-  static_assert(DNS >= 2 && DNS <= 4, "pipeline depth");
-  static_assert(DK == 32 || DK == 64, "stage depth");
+  constexpr int AW = AI / NWV, BW = (BI + NWV - 1) / NWV;  // ... per wave
+  constexpr int LPT = AW + BW;
+  static_assert(DNS >= 2 && (DNS - 1) * LPT < 64, "pipeline depth, vmcnt range");
   static_assert(AI % NWV == 0, "A tile must split evenly over the waves");
-  // Operand stages (A then B); after the K loop the same LDS stages the
-  // output tile for the row-contiguous stores of the epilogue.
-  constexpr int OPS = DNS * (BM + BN) * DK, STG = NWV * 32 * STAGED_LD<BN / WN>;
+  // Operand stages (A then B; where the B loads do not split evenly over the
+  // waves, the surplus ones write zeros to a spare slot, so that every wave
+  // counts the same loads per tile); after the K loop the same LDS stages
+  // the output tile for the row-contiguous stores of the epilogue.
+  constexpr bool SPARE = BI % NWV != 0;
+  constexpr int OPS = DNS * (BM + BN) * DK + (SPARE ? 512 : 0);
+  constexpr int STG = NWV * 32 * STAGED_LD<BN / WN>;
   __shared__ __attribute__((aligned(1024))) bf16 smem[OPS > STG ? OPS : STG];
   bf16* const As = smem;
   bf16* const Bs = smem + DNS * BM * DK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  bf16* const spare = smem + DNS * (BM + BN) * DK;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uni(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int tiles_n = (a.N + BN - 1) / BN;
+  // consecutive tiles on one XCD (blocks are dealt round-robin over 8)
   int bid = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) bid = (bid & 7) * (nb >> 3) + (bid >> 3);
+  {
+    const int nb = gridDim.x, q = nb >> 3, r = nb & 7, x = bid & 7;
+    bid = x * q + min(x, r) + (bid >> 3);
+  }
   // split-K: blocks split * tiles .. cover K tiles [kb, ke) of their output tile
-  const int tiles = (nb / a.ksplit), split = bid / tiles;
+  const int tiles = gridDim.x / a.ksplit, split = uni(bid / tiles);
   bid -= split * tiles;
   const int tm = bid / tiles_n, tn = bid - tm * tiles_n;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = uni(tm * BM), n0 = uni(tn * BN);
 
   // Rows and chunks this lane fetches: A load j of this wave is tile load
-  // i = wave * AW + j (rows RPL i ..); B load j is i = wave + NWV j.
+  // i = wave * AW + j (rows RPL i ..); B load j is i = wave + NWV j.  A row
+  // keeps its input pixel under the centre tap (UP: image base and output
+  // position) and the taps outside the image (bit 9: a tap that always is).
   const int lrow = lane / CPR, lslot = lane % CPR;
-  const int Ho = a.seg[0].Ho, Wo = a.seg[0].Wo, hwo = Ho * Wo;
-  int ra0[AW], ra1[AW], achunk[AW];
+  const int Hi = a.seg[0].Hi, Wi = a.seg[0].Wi, Ho = a.seg[0].Ho, Wo = a.seg[0].Wo, hwo = Ho * Wo;
+  const int stride = a.seg[0].stride;
+  int pix[AW], pyx[UP ? AW : 1], nmask[AW], voffA[AW];
 #pragma unroll
   for (int j = 0; j < AW; ++j) {
-    const int r = RPL * (wave * AW + j) + lrow;
-    const int m = m0 + r;
-    achunk[j] = lslot ^ swz<CPR>(r);
-    if constexpr (MODE == 1) {
-      const int p = m % hwo, oy = p / Wo, ox = p - oy * Wo;
-      int mk = 0;
+    const int m = m0 + RPL * (wave * AW + j) + lrow;
+    const int img = m / hwo, p = m - img * hwo, oy = p / Wo, ox = p - oy * Wo;
+    int mk = 0;
 #pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const int iy = oy + t / 3 - 1, ix = ox + t % 3 - 1;
-        if (iy >= 0 && iy < Ho && ix >= 0 && ix < Wo) mk |= 1 << t;
-      }
-      ra0[j] = m;
-      ra1[j] = m < a.M ? mk : 0;
-    } else {
-      const int img = m / hwo, p = m - img * hwo, oy = p / Wo, ox = p - oy * Wo;
-      ra0[j] = img * a.seg[0].Hi * a.seg[0].Wi;
-      ra1[j] = m < a.M ? (oy << 16) | ox : -1;
+    for (int t = 0; t < 9; ++t) {
+      const int iy = oy * stride + t / 3 - 1, ix = ox * stride + t % 3 - 1;
+      if (iy >= 0 && iy < (UP ? 2 * Hi : Hi) && ix >= 0 && ix < (UP ? 2 * Wi : Wi)) mk |= 1 << t;
     }
+    nmask[j] = m < a.M ? ~mk : -1;
+    pix[j] = UP ? img * Hi * Wi : img * Hi * Wi + oy * stride * Wi + ox * stride;
+    if constexpr (UP) pyx[j] = (oy << 16) | ox;
   }
+  // byte of the 16-byte chunk this lane fetches in tile load i
+  auto chunk16 = [&](int i) __attribute__((always_inline)) { return 16 * (lslot ^ swz<CPR>(RPL * i + lrow)); };
   const __amdgpu_buffer_rsrc_t bres = make_rsrc(a.B, (long)a.N * a.ldb * 2);
-  int boff[BW];
+  int voffB[BW];
 #pragma unroll
   for (int j = 0; j < BW; ++j) {
-    const int i = wave + NWV * j;
-    const int r = RPL * i + lrow;
-    const int n = n0 + r;
-    const int c = lslot ^ swz<CPR>(r);
-    boff[j] = (i < BI && n < a.N) ? n * a.ldb * 2 + c * 16 : OOB;
+    const int i = wave + NWV * j, n = n0 + RPL * i + lrow;
+    voffB[j] = (i < BI && n < a.N) ? n * a.ldb * 2 + chunk16(i) : OOB;
   }
 
-  const int nk_all = (a.K + DK - 1) / DK;  // K is a multiple of DK in modes 1, 2
-  const int per = (nk_all + a.ksplit - 1) / a.ksplit;
-  const int kb = split * per, ke = min(nk_all, kb + per);
-  // With TI (images larger than 8x8) the K tiles are visited channel block
-  // by channel block, all taps of a block in a row (the packed weights stay
-  // tap-major: a tile's weight columns follow from its tap and channel
-  // block), so consecutive tiles read the same input rows shifted by a tap
-  // and find them in L1 / L2; smaller images (a 256-row tile spans several)
-  // go tap by tap.  The order is a property of the layer, like the split.
-  constexpr bool tapin = TI;
-  int st_seg = 0, st_tap = 0, st_cb = 0;
-  {  // loader state at K tile kb
-    int kk = kb * DK;
-    if (MODE == 1 && kk >= a.seg[0].K) {
-      st_seg = 1;
-      kk -= a.seg[0].K;
-    }
-    const int gks = st_seg ? a.seg[1].ks : a.seg[0].ks, gcin = st_seg ? a.seg[1].cin : a.seg[0].cin;
-    const int i = kk / DK, taps = gks * gks;
-    if constexpr (tapin) {
-      st_cb = (i / taps) * DK;
-      st_tap = i - (i / taps) * taps;
-    } else {
-      st_tap = kk / gcin;
-      st_cb = kk - st_tap * gcin;
-    }
-  }
-  // The segment fields the refills read, read once as values (selected
-  // per tile rather than re-read from the kernel arguments: the scalar
-  // loads of a re-read stall the large tiles' loop on their waits).
+  const int nk_all = (a.K + DK - 1) / DK;  // K is a multiple of DK
+  const int per = uni((nk_all + a.ksplit - 1) / a.ksplit);
+  const int kb = split * per, nk = max(min(nk_all, kb + per) - kb, 0);
+
+  // The segment fields the runs read, read once and selected as values
+  // (selecting between lvalues would keep them in scratch).
   const void *g0s0 = a.seg[0].src0, *g0s1 = a.seg[0].src1, *g1s0 = a.seg[1].src0, *g1s1 = a.seg[1].src1;
-  const int g0cin = a.seg[0].cin, g0ks = a.seg[0].ks, g0c0 = a.seg[0].c0, g0c1 = a.seg[0].c1, g0py = a.seg[0].py,
-            g0px = a.seg[0].px, g0K = a.seg[0].K, gM = a.M;
-  const int g1cin = a.seg[1].cin, g1ks = a.seg[1].ks, g1c0 = a.seg[1].c0, g1c1 = a.seg[1].c1, g1py = a.seg[1].py,
-            g1px = a.seg[1].px;
-  // Issue the loads of K tile kt into stage `stg` (tiles are issued in
-  // order).  `live` false: every offset out of range (zeros, no memory
-  // access), for the large tiles' refills past the last tile.
-  auto issue = [&](int kt, int stg, bool live = true) {
-    (void)kt;
-    const bool s1 = MODE == 1 && st_seg;
-    const int gcin = s1 ? g1cin : g0cin, gks = s1 ? g1ks : g0ks;
-    const int gc0 = s1 ? g1c0 : g0c0, gc1 = s1 ? g1c1 : g0c1;
-    const void* gs0 = s1 ? g1s0 : g0s0;
-    const void* gs1 = s1 ? g1s1 : g0s1;
-    const int tap = st_tap, cb = st_cb;
-    const int k0 = (s1 ? g0K : 0) + tap * gcin + cb;  // the tile's weight columns
-    if constexpr (tapin) {
-      if (++st_tap == gks * gks) {
-        st_tap = 0;
-        st_cb += DK;
-        if (st_cb >= gcin) {
-          st_cb = 0;
-          st_seg = 1;
-        }
+  const int g0ks = a.seg[0].ks, g0cin = a.seg[0].cin, g0c0 = a.seg[0].c0, g0c1 = a.seg[0].c1, g0py = a.seg[0].py,
+            g0px = a.seg[0].px, g0K = a.seg[0].K;
+  const int g1ks = a.seg[1].ks, g1cin = a.seg[1].cin, g1c0 = a.seg[1].c0, g1c1 = a.seg[1].c1;
+  KPos s;
+  auto set_source = [&](int cs2) __attribute__((always_inline)) {
+    s.cs2 = cs2;
+    if constexpr (!UP) {
+#pragma unroll
+      for (int j = 0; j < AW; ++j) voffA[j] = pix[j] * cs2 + chunk16(wave * AW + j);
+    }
+  };
+  // Start the run that holds (segment, tap, channel).
+  auto place = [&](int seg, int tap, int cb) __attribute__((always_inline)) {
+    const bool s1 = seg != 0;
+    const int ks = pick(s1, g1ks, g0ks), cin = pick(s1, g1cin, g0cin), c0 = pick(s1, g1c0, g0c0);
+    const int c1 = pick(s1, g1c1, g0c1);
+    const int py = g0py, px = g0px;  // (an upsample phase has one segment)
+    const bool in0 = cb < c0;
+    const char* src = (const char*)pick(in0, pick(s1, g1s0, g0s0), pick(s1, g1s1, g0s1));
+    const int cs = pick(in0, c0, c1);
+    // tap displacement; its bit in the 3x3 in-image mask (a 1x1 tap is the
+    // centre; an upsample phase's 2x2 taps are four of the nine)
+    const int ky = ks == 1 ? 1 : (ks == 3 ? tap / 3 : py + (tap >> 1));
+    const int kx = ks == 1 ? 1 : (ks == 3 ? tap % 3 : px + (tap & 1));
+    const int dpix = UP ? 0 : (ky - 1) * Wi + kx - 1;
+    s.ab = src + ((long)dpix * cs + (in0 ? cb : cb - c0)) * 2;
+    s.boff = (pick(s1, g0K, 0) + tap * cin + cb) * 2;
+    s.sh = 31 - (3 * ky + kx);
+    s.ti = TI && ks > 1;
+    if (s.ti) {
+      s.left = ks * ks - tap;
+      s.tp = tap;
+      s.da = UP ? 0 : 2 * cs;
+      s.daw = UP ? 0 : (Wi - ks + 1) * 2 * cs;
+      s.db = 2 * cin;
+      s.dsh = 1;
+      s.dshw = 4 - ks;
+      s.wm = ks == 3 ? 0x24 : 0x2;
+    } else {
+      s.left = (pick(in0, c0, cin) - cb) / DK;
+      s.tp = 0;
+      s.da = s.daw = s.db = 2 * DK;
+      s.dsh = s.dshw = s.wm = 0;
+    }
+    s.ab = uni(s.ab);
+    s.boff = uni(s.boff);
+    s.sh = uni(s.sh);
+    s.da = uni(s.da);
+    s.daw = uni(s.daw);
+    s.db = uni(s.db);
+    s.dsh = uni(s.dsh);
+    s.dshw = uni(s.dshw);
+    s.wm = uni(s.wm);
+    s.left = uni(min(s.left, s.togo));
+    s.seg = seg;
+    s.cb = cb;
+    s.tap = tap;
+    if (s.cs2 != 2 * cs) set_source(2 * cs);
+  };
+  // The run after the current one, or past the end.
+  auto next_run = [&]() __attribute__((always_inline)) {
+    if (s.togo == 0) {
+      s.dead = OOB;
+      s.sh = 31 - 9;
+      s.da = s.daw = s.db = s.dsh = s.dshw = 0;
+      s.left = 0x7FFFFFFF;
+      return;
+    }
+    const bool s1 = s.seg != 0;
+    const int ks = pick(s1, g1ks, g0ks), cin = pick(s1, g1cin, g0cin), c0 = pick(s1, g1c0, g0c0);
+    int seg = s.seg, tap = 0, cb = 0;
+    if (s.ti) {
+      cb = s.cb + DK;
+      if (cb == cin) {
+        cb = 0;
+        ++seg;
       }
     } else {
-      st_cb += DK;
-      if (st_cb >= gcin) {
-        st_cb = 0;
-        if (++st_tap == gks * gks) {
-          st_tap = 0;
-          st_seg = 1;
+      tap = s.tap;
+      cb = pick(s.cb < c0, c0, cin);
+      if (cb == cin) {
+        cb = 0;
+        if (++tap == ks * ks) {
+          tap = 0;
+          ++seg;
         }
       }
     }
-    const bool in0 = cb < gc0;
-    const int cs = in0 ? gc0 : gc1, cbase = 2 * (in0 ? cb : cb - gc0);
-    bf16* adst = As + stg * BM * DK;
-    if constexpr (MODE == 1) {
-      const __amdgpu_buffer_rsrc_t ares = make_rsrc(in0 ? gs0 : gs1, (long)gM * cs * 2);
-      // tap offset (dy, dx) and its bit in the 3x3 in-image mask (a 1x1 tap
-      // is the centre; an upsample phase's 2x2 taps are four of the nine)
-      const int gpy = s1 ? g1py : g0py, gpx = s1 ? g1px : g0px;
-      // (arithmetic rather than selects, so the refill has no branch: a
-      // masked element gets bit 31 set, beyond every source's size)
-      const int t3 = tap / 3, is3 = gks == 3, is2 = gks == 2;
-      const int tdy = is3 * (t3 - 1) + is2 * (gpy - 1 + (tap >> 1));
-      const int tdx = is3 * (tap - 3 * t3 - 1) + is2 * (gpx - 1 + (tap & 1));
-      const int t9 = (tdy + 1) * 3 + tdx + 1;
-      const int dpix = tdy * Wo + tdx;
-      const int dead = (int)!live << 31;
+    place(seg, tap, cb);
+  };
+  // Issue the loads of the next K tile into stage `stg`.
+  auto issue = [&](int stg) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t ares = make_rsrc(s.ab, 0x7FFFFFFF);
+    bf16* adst = As + stg * BM * DK + wave * AW * 512;
 #pragma unroll
-      for (int j = 0; j < AW; ++j) {
-        const int off = ((ra0[j] + dpix) * cs * 2 + cbase + achunk[j] * 16) | (~(ra1[j] >> t9) << 31) | dead;
-        dma16(ares, adst + (wave * AW + j) * 512, off);
+    for (int j = 0; j < AW; ++j) {
+      int v = voffA[j];
+      if constexpr (UP) {
+        const int t9 = 31 - s.sh, ky = t9 / 3 - 1, kx = t9 % 3 - 1;
+        const int iy = ((pyx[j] >> 16) + ky) >> 1, ix = ((pyx[j] & 0xFFFF) + kx) >> 1;
+        v = (pix[j] + iy * Wi + ix) * s.cs2 + chunk16(wave * AW + j);
       }
-    } else {
-      const ASeg& g = a.seg[0];
-      const long npix = (long)(a.M / hwo) * g.Hi * g.Wi;
-      const __amdgpu_buffer_rsrc_t ares = make_rsrc(gs0, npix * cs * 2);
-      const int ky = tap / 3 - 1, kx = tap % 3 - 1;
-#pragma unroll
-      for (int j = 0; j < AW; ++j) {
-        const int oy = ra1[j] >> 16, ox = ra1[j] & 0xFFFF;
-        int iy, ix;
-        bool ok;
-        if (g.up) {
-          iy = oy + ky;
-          ix = ox + kx;
-          ok = iy >= 0 && iy < 2 * g.Hi && ix >= 0 && ix < 2 * g.Wi;
-          iy >>= 1;
-          ix >>= 1;
-        } else {
-          iy = oy * g.stride + ky;
-          ix = ox * g.stride + kx;
-          ok = iy >= 0 && iy < g.Hi && ix >= 0 && ix < g.Wi;
-        }
-        ok = ok && ra1[j] >= 0 && live;
-        const int off = ok ? (ra0[j] + iy * g.Wi + ix) * cs * 2 + cbase + achunk[j] * 16 : OOB;
-        dma16(ares, adst + (wave * AW + j) * 512, off);
-      }
+      dma16(ares, adst + j * 512, ((nmask[j] << s.sh) & OOB) | (UP ? v & 0x7FFFFFFF : v), 0);
     }
     bf16* bdst = Bs + stg * BN * DK;
+    const int boff = uni(s.boff);
 #pragma unroll
     for (int j = 0; j < BW; ++j) {
       const int i = wave + NWV * j;
-      if (BI % NWV == 0 || i < BI)  // wave-uniform (an OOB row stays beyond the end)
-        dma16(bres, bdst + i * 512, (boff[j] + 2 * k0) | ((int)!live << 31));
+      dma16(bres, (SPARE && i >= BI) ? spare : bdst + i * 512, voffB[j] | s.dead, boff);
+    }
+  };
+  auto advance = [&]() __attribute__((always_inline)) {
+    --s.togo;
+    if (--s.left == 0) {
+      next_run();
+    } else {
+      const bool w = (s.wm >> s.tp) & 1;
+      s.ab += pick(w, s.daw, s.da);
+      s.sh -= pick(w, s.dshw, s.dsh);
+      s.boff += s.db;
+      ++s.tp;
     }
   };
 
@@ -922,151 +913,151 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int nk = ke - kb;
+  s.cs2 = -1;
+  s.dead = 0;
+  s.togo = nk;
+  if (nk > 0) {  // the run at K tile kb
+    int kk = kb * DK, seg = 0;
+    if (kk >= g0K) {
+      seg = 1;
+      kk -= g0K;
+    }
+    const int ks = pick(seg != 0, g1ks, g0ks), cin = pick(seg != 0, g1cin, g0cin), taps = ks * ks;
+    if (TI && taps > 1) {
+      const int i = kk / DK, c = i / taps;
+      place(seg, uni(i - c * taps), uni(c * DK));
+    } else {
+      const int tap = uni(kk / cin);
+      place(seg, tap, kk - tap * cin);
+    }
+  } else {
+    s.ab = (const char*)g0s0;
+    s.boff = s.tp = 0;
+    s.seg = s.cb = s.tap = 0;
+    s.ti = false;
+    set_source(0);
+    next_run();
+  }
+
   const int lr = lane & 31, lh = lane >> 5;
   const int arow = wm * (BM / WM) + lr, brow = wn * (BN / WN) + lr;
-  if constexpr (TM * TN > 10) {
-    // Large wave tiles run one wave per SIMD, so nothing else hides the
-    // K-step barrier or the fragment reads: the loop is software-pipelined.
-    // All DNS stages are in flight; the fragments of substep ks + 1 are
-    // read before the products of substep ks, and the first fragments of
-    // tile kt + 1 (after its wait and the barrier) before the last products
-    // of tile kt.  Tile kt + DNS refills the stage of tile kt once every
-    // wave has passed that barrier (its reads of tile kt have completed).
-    constexpr int KS = DK / 16;
-    static_assert(KS % 2 == 0, "fragment sets alternate per substep");
-    bf16x8 fa[2][TM], fb[2][TN];
-    auto readf = [&](int stg, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
-      const bf16* Ab = As + stg * BM * DK;
-      const bf16* Bb = Bs + stg * BN * DK;
-      const int ch = 2 * ks + lh;
+  // fragment of row r, chunk c: element r DK + 8 (c ^ swz(r)); rows 32 apart share the swizzle
+  constexpr int KS = DK / 16;  // 16-deep substeps per tile
+  int fa_off[KS], fb_off[KS];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int r = arow + i * 32;
-        af[i] = *reinterpret_cast<const bf16x8*>(&Ab[r * DK + 8 * (ch ^ swz<CPR>(r))]);
-      }
+  for (int k = 0; k < KS; ++k) {
+    fa_off[k] = arow * DK + 8 * ((2 * k + lh) ^ swz<CPR>(arow));
+    fb_off[k] = brow * DK + 8 * ((2 * k + lh) ^ swz<CPR>(brow));
+  }
+  // Fragment sets: the smallest wave tiles (at most two products a substep)
+  // hold a whole tile's fragments twice, so an LDS read has a tile's products
+  // to land; the others two substeps', unless two blocks of 64 x 160 waves
+  // share a CU, which leaves no registers for a second set.
+  constexpr bool WT = TM * TN <= 2, PF = !WT && !(TM * TN == 10 && MINB > 1);
+  constexpr int NF = WT ? 2 * KS : (PF ? 2 : 1);
+  bf16x8 fa[NF][TM], fb[NF][TN];
+  auto readf = [&](int stg, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
+    const bf16* Ab = As + stg * BM * DK + fa_off[ks];
+    const bf16* Bb = Bs + stg * BN * DK + fb_off[ks];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int r = brow + j * 32;
-        bfr[j] = *reinterpret_cast<const bf16x8*>(&Bb[r * DK + 8 * (ch ^ swz<CPR>(r))]);
-      }
+    for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const bf16x8*>(Ab + i * 32 * DK);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(Bb + j * 32 * DK);
+  };
+  auto products = [&](int cur) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
+  };
+  auto prologue = [&](int n) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int p = 0; p < n; ++p) {
+      issue(p);
+      advance();
+    }
+  };
+  // The wait and barrier after which tile kt + 1 may be read and the stage of
+  // tile kt refilled: its loads have landed (DNS - 2 tiles stay in flight) and
+  // this wave's reads of tile kt are complete.
+  auto next_ready = [&]() __attribute__((always_inline)) {
+    wait_vmcnt<(DNS - 2) * LPT>();
+    wait_lgkm0();
+    stage_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int st = 0;  // stage of the tile
+  if constexpr (WT) {
+    prologue(DNS);
+    wait_vmcnt<(DNS - 1) * LPT>();  // tile 0 has landed
+    stage_barrier();
+    static_for<0, KS>([&](auto K) { readf(0, K.value, fa[K.value], fb[K.value]); });
+    auto tile = [&](auto CUR) __attribute__((always_inline)) {
+      constexpr int cur = CUR.value * KS, nxt = KS - cur;
+      const int nst = st + 1 == DNS ? 0 : st + 1;
+      next_ready();
+      static_for<0, KS>([&](auto K) { readf(nst, K.value, fa[nxt + K.value], fb[nxt + K.value]); });
+      issue(st);
+      static_for<0, KS>([&](auto K) { products(cur + K.value); });
+      advance();
+      st = nst;
     };
-    // Every stage refill is issued, past the last tile as an all-out-of-range
-    // load (zeros into a stage no product reads), so the loop body has no
-    // branch and every wait counts the same DNS - 2 tiles in flight.
-    static_assert(AI % NWV == 0 && BI % NWV == 0, "every wave issues the same loads");
-#pragma unroll
-    for (int p = 0; p < DNS; ++p) issue(kb + p, p, p < nk);
-    wait_vmcnt<(DNS - 1) * LPT_MIN>();  // tile 0 has landed
+    for (int kt = 0; kt < nk; kt += 2) {
+      tile(IC<0>{});
+      if (kt + 1 < nk) tile(IC<1>{});
+    }
+  } else if constexpr (PF) {
+    prologue(DNS);
+    wait_vmcnt<(DNS - 1) * LPT>();  // tile 0 has landed
     stage_barrier();
     readf(0, 0, fa[0], fb[0]);
-    auto products = [&](int cur) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-    };
-    // The kernel arguments are loaded here, before the wait below (left to
-    // the compiler, some load lazily and are still in flight at the loop;
-    // scalar loads return out of order, so every wait for an LDS read in
-    // the loop would then wait for all of them).  After it the loop's LDS
-    // reads are counted in order: a product waits only for its own
-    // fragments.
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const ASeg& sg = a.seg[g];
-      asm volatile("" ::"s"(sg.src0), "s"(sg.src1), "s"(sg.cin), "s"(sg.ks), "s"(sg.c0), "s"(sg.c1));
-      asm volatile("" ::"s"(sg.K), "s"(sg.py), "s"(sg.px), "s"(sg.Hi), "s"(sg.Wi), "s"(sg.stride), "s"(sg.up));
-    }
-    {
-      const Epi& e = a.epi;
-      asm volatile("" ::"s"(e.bias), "s"(e.tbias), "s"(e.tb_ld), "s"(e.tb_off), "s"(e.hw), "s"(e.resid), "s"(e.ldr));
-      asm volatile("" ::"s"(e.out), "s"(e.ldo), "s"(e.geglu), "s"(e.qcols), "s"(e.qscale), "s"(e.phase));
-      asm volatile("" ::"s"(e.ph_h), "s"(e.ph_w), "s"(e.rowscale), "s"(a.M), "s"(a.N), "s"(e.out_f32));
-    }
-    wait_lgkm0();
-    __builtin_amdgcn_sched_barrier(0);
-    // every tile but the last: the last substep reads the next tile
-    for (int kt = 0; kt + 1 < nk; ++kt) {
+    for (int kt = 0; kt < nk; ++kt) {
+      const int nst = st + 1 == DNS ? 0 : st + 1;
       static_for<0, KS>([&](auto KSI) {
         constexpr int ks = KSI.value, cur = ks & 1, nxt = cur ^ 1;
         if constexpr (ks + 1 < KS) {
-          readf(kt % DNS, ks + 1, fa[nxt], fb[nxt]);
-          __builtin_amdgcn_sched_barrier(0);  // the reads go out before the products
+          readf(st, ks + 1, fa[nxt], fb[nxt]);
+          if constexpr (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);  // the reads go out before the products
           products(cur);
         } else {
-          __builtin_amdgcn_sched_barrier(0);  // the previous substep's products stay above
-          // tiles issued after kt + 1: kt + 2 .. kt + DNS - 1
-          wait_vmcnt<(DNS - 2) * LPT_MIN>();
-          wait_lgkm0();  // this wave's reads of tile kt are complete
-          stage_barrier();
-          __builtin_amdgcn_sched_barrier(0);
-          readf((kt + 1) % DNS, 0, fa[nxt], fb[nxt]);
-          issue(kb + kt + DNS, kt % DNS, kt + DNS < nk);
+          if constexpr (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);  // the previous products stay above
+          next_ready();
+          readf(nst, 0, fa[nxt], fb[nxt]);
+          issue(st);
           products(cur);
-          // each fragment read, then each refill load, beside a product
-#pragma unroll
-          for (int q = 0; q < TM + TN; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+          if constexpr (TM * TN > 4) {
+            // the fragment reads, then the refill loads, spread over the products
+            constexpr int NP = TM * TN, NR = TM + TN;
+            constexpr int LP = NP > NR ? NP - NR : 1;  // products left for the loads
+            static_for<0, NP>([&](auto Q) {
+              constexpr int q = Q.value, l = q - (NP - LP);
+              if constexpr (q < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+              if constexpr (l >= 0 && (l + 1) * LPT / LP > l * LPT / LP)
+                __builtin_amdgcn_sched_group_barrier(0x020, (l + 1) * LPT / LP - l * LPT / LP, 0);  // VMEM read
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+            });
           }
-#pragma unroll
-          for (int q = 0; q < AW + BW; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          }
+          advance();
         }
       });
+      st = nst;
     }
-    if (nk > 0) {
-      static_for<0, KS>([&](auto KSI) {  // the last tile
-        constexpr int ks = KSI.value, cur = ks & 1, nxt = cur ^ 1;
-        if constexpr (ks + 1 < KS) readf((nk - 1) % DNS, ks + 1, fa[nxt], fb[nxt]);
-        products(cur);
-      });
-    }
-    wait_vmcnt<0>();  // the refills past the last tile have landed
   } else {
-#pragma unroll
-    for (int p = 0; p < DNS - 1; ++p)
-      if (p < nk) issue(kb + p, p);
+    prologue(DNS - 1);
     for (int kt = 0; kt < nk; ++kt) {
-      // Tile kt must have landed; the tiles issued after it may still be in
-      // flight (at most DNS-2 of them, fewer near the end of K).
-      const int ahead = min(DNS - 2, nk - 1 - kt);
-      if (ahead >= 2)
-        wait_vmcnt<2 * LPT_MIN>();
-      else if (ahead == 1)
-        wait_vmcnt<LPT_MIN>();
-      else
-        wait_vmcnt<0>();
-      stage_barrier();
-      if (kt + DNS - 1 < nk) issue(kb + kt + DNS - 1, (kt + DNS - 1) % DNS);
-      const bf16* Ab = As + (kt % DNS) * BM * DK;
-      const bf16* Bb = Bs + (kt % DNS) * BN * DK;
-#pragma unroll
-      for (int ks = 0; ks < DK / 16; ++ks) {
-        const int ch = 2 * ks + lh;
-        bf16x8 af[TM], bfr[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int r = arow + i * 32;
-          af[i] = *reinterpret_cast<const bf16x8*>(&Ab[r * DK + 8 * (ch ^ swz<CPR>(r))]);
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int r = brow + j * 32;
-          bfr[j] = *reinterpret_cast<const bf16x8*>(&Bb[r * DK + 8 * (ch ^ swz<CPR>(r))]);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-      }
+      next_ready();  // (here: tile kt may be read, the stage of tile kt - 1 refilled)
+      static_for<0, KS>([&](auto KSI) {
+        constexpr int ks = KSI.value;
+        readf(st, ks, fa[0], fb[0]);
+        if constexpr (ks == 0) issue(st == 0 ? DNS - 1 : st - 1);
+        products(0);
+      });
+      advance();
+      st = st + 1 == DNS ? 0 : st + 1;
     }
   }
+  wait_vmcnt<0>();  // the refills past the last tile have landed
   if (a.ksplit > 1) {
     // raw fp32 partial sums; the reduction kernel applies the epilogue
     const int lr = lane & 31, hq = 4 * (lane >> 5);
@@ -1089,14 +1080,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
     });
     return;
   }
-  if constexpr (TM * TN > 10) {
-    // large wave tiles: the host sends only layers this epilogue covers
-    static_assert(NWV * 32 * SLAB_LD<BN / WN> * 4 <= (int)sizeof(smem), "slabs fit the operand stages");
-    __syncthreads();  // every wave is done with the operand stages
-    epilogue_slab<BM, BN, WM, WN>(a, acc, m0, n0, wm, wn, lane,
-                                  reinterpret_cast<float*>(smem) + wave * 32 * SLAB_LD<BN / WN>);
-    return;
-  } else {
+  {
     static_assert(32 * (BN / WN) <= 32 * STAGED_LD<BN / WN>, "transposed staging fits the region");
     const bool vt_ok = a.epi.vt_out && a.epi.vt_col0 % (BN / WN) == 0 && a.epi.vt_hw % 32 == 0 && a.epi.vt_ld % 8 == 0;
     if ((!a.epi.vt_out || vt_ok) && !a.epi.out_f32 && (!a.epi.resid || !a.epi.geglu)) {
@@ -1236,25 +1220,23 @@ static void launch_bf16(const GemmArgs& a, hipStream_t s) {
 
 // Direct-to-LDS kernel for the uniform-tap modes; false if the layer needs
 // the register-staged loader.
-template <int BM, int BN, int WM, int WN, int DNS, int MINB, int DK = DKS, bool UNIFORM_ONLY = false>
+template <int BM, int BN, int WM, int WN, int DK, int DNS, int MINB>
 static bool launch_dma(const GemmArgs& a, hipStream_t s) {
-  const int mode = loader_mode(a, DK);
-  if (mode == 0 || (UNIFORM_ONLY && mode != 1) || (DK != DKS && a.ksplit > 1)) return false;
+  // (whole tiles of columns only: the staged epilogues do not mask columns)
+  if (loader_mode(a, DK) == 0 || a.N % BN) return false;
   const long blocks = (long)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * a.ksplit;
   const dim3 g((unsigned)blocks), b(64 * WM * WN);
   // K order (see the kernel): channel block outer, taps inner on images
   // larger than 8x8.
-  const bool ti = (long)a.seg[0].Ho * a.seg[0].Wo > 64;
-  if (mode == 1 && ti)
-    gemm_bf16_dma_kernel<BM, BN, WM, WN, 1, DNS, MINB, DK, true><<<g, b, 0, s>>>(a);
-  else if (mode == 1)
-    gemm_bf16_dma_kernel<BM, BN, WM, WN, 1, DNS, MINB, DK, false><<<g, b, 0, s>>>(a);
-  else if constexpr (!UNIFORM_ONLY) {
-    if (ti)
-      gemm_bf16_dma_kernel<BM, BN, WM, WN, 2, DNS, MINB, DK, true><<<g, b, 0, s>>>(a);
-    else
-      gemm_bf16_dma_kernel<BM, BN, WM, WN, 2, DNS, MINB, DK, false><<<g, b, 0, s>>>(a);
-  }
+  const bool ti = (long)a.seg[0].Ho * a.seg[0].Wo > 64, up = a.seg[0].up != 0;
+  if (!up && ti)
+    gemm_bf16_dma_kernel<BM, BN, WM, WN, false, DK, DNS, MINB, true><<<g, b, 0, s>>>(a);
+  else if (!up)
+    gemm_bf16_dma_kernel<BM, BN, WM, WN, false, DK, DNS, MINB, false><<<g, b, 0, s>>>(a);
+  else if (ti)
+    gemm_bf16_dma_kernel<BM, BN, WM, WN, true, DK, DNS, MINB, true><<<g, b, 0, s>>>(a);
+  else
+    gemm_bf16_dma_kernel<BM, BN, WM, WN, true, DK, DNS, MINB, false><<<g, b, 0, s>>>(a);
   if (a.ksplit > 1) {
     const long n = (long)a.M * (a.N / 4);
     splitk_reduce_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(a);
@@ -1276,11 +1258,63 @@ int gemm_ksplit(const GemmArgs& a) {
   return hw <= 64 ? 4 : 2;
 }
 
-// Tile choice: the widest N tile that divides N (320 and 160 cover every
-// SD-1.5 / SDXL width: 320, 640, 1280 and their 2x, 3x, 4x, 8x), then the
-// tallest M tile that still gives every CU about two blocks.  The tile shape
-// never changes a row's K order, so only the split factor (a function of the
-// layer shape) decides a row's bits.
+// Tiles of the 64-deep direct-to-LDS kernel.  A block's time is modelled as
+// eb + nk * t us for its nk K tiles, t1 for a block alone on its CU and tf
+// when occ blocks share it (fitted to 149 conv and linear shapes of 64 to
+// 262144 rows; the modelled choice is within 2 % of the best tile on average,
+// 15 % at worst).  The tile never changes a row's K order, so every tile gives
+// the same bits and the choice may follow the row count.
+struct Tile64 {
+  int bm, bn, occ;
+  float t1, tf, eb;
+};
+static const Tile64 kTiles64[] = {
+    {64, 64, 2, 0.224f, 0.402f, 4.6f},     // 4 waves of 32 x 32, four stages
+    {128, 64, 2, 0.343f, 0.606f, 7.4f},    // 4 waves of 64 x 32, three stages
+    {128, 128, 2, 0.594f, 0.979f, 10.9f},  // 4 waves of 64 x 64, two stages
+    {128, 160, 2, 0.668f, 1.344f, 12.4f},  // 4 waves of 32 x 160, two stages
+    {256, 256, 1, 1.130f, 1.861f, 16.9f},  // 8 waves of 128 x 64, two stages
+    {256, 320, 1, 1.327f, 2.340f, 19.8f},  // 8 waves of 64 x 160, two stages
+};
+
+// Index of the tile with the smallest modelled time, -1 when none divides N.
+static int pick_tile64(long M, long N, long K, int ksplit) {
+  const float nk = (float)((K / 64 + ksplit - 1) / ksplit);
+  int best = -1;
+  float tbest = 0.f;
+  for (int i = 0; i < (int)(sizeof(kTiles64) / sizeof(kTiles64[0])); ++i) {
+    const Tile64& t = kTiles64[i];
+    if (N % t.bn) continue;
+    const long blocks = (M + t.bm - 1) / t.bm * (N / t.bn) * ksplit, slots = 256L * t.occ;
+    const long full = blocks / slots, rest = (blocks - full * slots + 255) / 256;  // rest: blocks per CU of the last round
+    const float tr = t.occ > 1 ? t.t1 + (t.tf - t.t1) * (float)(rest - 1) / (float)(t.occ - 1) : t.t1;
+    // (one block of 8 waves fills a CU: its rounds overlap only at their ends)
+    const float us = (float)full * (nk * t.tf + t.eb) + (rest > 0 ? nk * tr + t.eb : 0.f);
+    if (best < 0 || us < tbest) {
+      best = i;
+      tbest = us;
+    }
+  }
+  return best;
+}
+
+static bool launch_tile64(const GemmArgs& a, hipStream_t s) {
+  if (loader_mode(a, 64) == 0) return false;
+  switch (pick_tile64(a.M, a.N, a.K, a.ksplit)) {
+    case 0: return launch_dma<64, 64, 2, 2, 64, 4, 2>(a, s);
+    case 1: return launch_dma<128, 64, 2, 2, 64, 3, 2>(a, s);
+    case 2: return launch_dma<128, 128, 2, 2, 64, 2, 2>(a, s);
+    case 3: return launch_dma<128, 160, 4, 1, 64, 2, 2>(a, s);
+    case 4: return launch_dma<256, 256, 2, 4, 64, 2, 1>(a, s);
+    case 5: return launch_dma<256, 320, 4, 2, 64, 2, 1>(a, s);
+    default: return false;
+  }
+}
+
+// Tile choice: 64-deep tiles (above) where the loader allows them; else the
+// widest N tile that divides N, then the tallest M tile that still gives every
+// CU about two blocks.  Only the split factor and the stage depth, functions
+// of the layer shape, decide a row's K order and so its bits.
 hipError_t launch_gemm(DType dt, const GemmArgs& args, hipStream_t s) {
   GemmArgs a = args;
   if (a.ksplit < 1) a.ksplit = 1;
@@ -1307,41 +1341,22 @@ hipError_t launch_gemm(DType dt, const GemmArgs& args, hipStream_t s) {
   if (dt == BF16) {
     auto nblk = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     const long want = 2 * 256;
-    // Long-K layers of widths that are multiples of 256 (the 1280-wide
-    // levels) may take 256x256 tiles: four waves of 128x128 with the
-    // accumulators in AGPRs, one block per CU (3 x 32 KB stages), about 14 %
-    // faster per tile-product than two 256x160 blocks per CU.  With one
-    // block per CU the last wave of blocks can leave much of the chip idle,
-    // so they are taken only where their share of busy block slots, with
-    // that margin, is at least the narrower tiles' (two per CU).  Every
-    // tile gives the same bits, so the choice may follow the row count.
-    auto busy = [](long blocks, long slots) { return (double)blocks / (double)(((blocks + slots - 1) / slots) * slots); };
-    const long n_wide = nblk(256, 256) * a.ksplit;
-    const long n_alt = (a.N % 160 == 0 ? nblk(256, 160) : nblk(256, 128)) * a.ksplit;
-    if (a.N % 256 == 0 && a.K >= 2560 && n_wide >= 128 && 1.1 * busy(n_wide, 256) >= busy(n_alt, 512) &&
-        !a.epi.vt_out && !a.epi.out_f32 && !a.epi.geglu && !a.epi.rowscale && a.epi.qcols == 0 &&
-        launch_dma<256, 256, 2, 2, 3, 1, DKS, true>(a, s)) {
+    if (launch_tile64(a, s)) {
     } else if (a.N % 160 == 0) {
-      // 256x160 tiles through the direct-to-LDS pipeline whenever the loader
-      // is uniform: taller tiles cut the weight re-reads that dominate
-      // small-M layers.  Three K stages (two for the split-K layers) still
-      // leave LDS for two blocks per CU.  Otherwise register-staged 64-deep
-      // tiles, one block per CU.
+      // 32-deep stages: 256x160 tiles, three of them (2 x 80.9 KB of LDS: two
+      // blocks per CU); otherwise register-staged 64-deep tiles, one block per CU
       const bool big = nblk(256, 160) * a.ksplit >= want;
-      if (a.ksplit == 1 && nblk(256, 160) < 256 && launch_dma<64, 160, 2, 1, 2, 4>(a, s)) {
-        // short M (the context K/V projections): 64-row tiles, four blocks per CU
-      } else if (a.ksplit == 1 && launch_dma<256, 160, 4, 1, 3, 2>(a, s)) {
-        // three K stages (2 x 79.9 KB of LDS: still two blocks per CU)
-      } else if (launch_dma<256, 160, 4, 1, 2, 2>(a, s)) {
+      if (a.ksplit == 1 && nblk(256, 160) < 256 && launch_dma<64, 160, 2, 1, 32, 2, 4>(a, s)) {
+        // short M: 64-row tiles, four blocks per CU
+      } else if (launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s)) {
       } else if (big) {
         launch_bf16<256, 160, 64, 4, 1>(a, s);
       } else {
         launch_bf16<128, 160, 64, 4, 1>(a, s);
       }
-    } else if (a.N % 128 == 0 && a.ksplit == 1 && launch_dma<256, 128, 4, 1, 3, 2>(a, s)) {
-      // widths that are multiples of 128 but not of 160 (the VAE decoder's
-      // 128 / 256 / 512): the same direct-to-LDS pipeline in 256x128 tiles,
-      // waves of 64x128, three K stages (2 x 73.7 KB of LDS)
+    } else if (a.N % 128 == 0 && a.ksplit == 1 && launch_dma<256, 128, 4, 1, 32, 3, 2>(a, s)) {
+      // widths that are multiples of 128 but not of 160, 32-deep stages (the
+      // VAE decoder's conv_in): 256x128 tiles, waves of 64x128
     } else if (a.N % 128 == 0 || a.N > 64) {
       if (nblk(256, 128) >= want)
         launch_bf16<256, 128, 64, 2, 2>(a, s);

@@ -415,6 +415,56 @@ def test_conv_wide_tiles(ops, case):
         assert err <= TOL["bf16"], (i, err)
 
 
+TILE64_CASES = [
+    # n, H, W, c0, c1, cout, ks, stride, up: 64-deep K stages.  The whole batch
+    # takes one tile, its first image alone the 64x64 (width 160: 128x160) one;
+    # ragged row counts, so that the last row tile is partly empty.
+    (11, 53, 57, 64, 0, 64, 3, 1, 0),     # 128x64 (33231 rows)
+    (7, 71, 67, 64, 0, 128, 3, 1, 0),     # 128x128 (33299 rows), one channel block
+    (5, 61, 67, 64, 64, 160, 3, 1, 0),    # 128x160 only, concat sources
+    (33, 33, 31, 128, 64, 256, 3, 1, 0),  # 256x256 (33759 rows), concat sources
+    (9, 61, 61, 64, 0, 320, 3, 1, 0),     # 256x320 (33489 rows)
+    (130, 8, 8, 64, 128, 1280, 3, 1, 0),  # 256x256 on 8x8 images (taps outer), concat sources
+    (33, 32, 32, 64, 0, 256, 3, 2, 0),    # stride 2
+    (9, 30, 31, 64, 0, 320, 3, 1, 1),     # 256x320, upsampling
+    (1, 1, 33003, 192, 64, 320, 1, 1, 0),  # linear, concat sources
+    (2, 3, 1, 64, 0, 64, 3, 1, 0),        # six rows
+    (1, 1, 1, 64, 0, 64, 1, 1, 0),        # one row, one K stage
+]
+
+
+@pytest.mark.parametrize("case", TILE64_CASES)
+def test_conv_tiles64(ops, case):
+    """Every tile of the 64-deep direct-to-LDS kernel: the first image gets the
+    same bits in the whole batch as alone, and the last one (ragged rows)
+    matches the oracle."""
+    n, H, W, c0, c1, cout, ks, stride, up = case
+    log(f"tiles64 {case}")
+    rng = np.random.default_rng(hash(case) % 2**32)
+    x0 = _vals(rng, (n, H, W, c0), "bf16")
+    x1 = _vals(rng, (n, H, W, c1), "bf16") if c1 else None
+    w = _vals(rng, (cout, c0 + c1, ks, ks), "bf16", 1.0 / math.sqrt(ks * ks * (c0 + c1)))
+    b = rng.standard_normal(cout).astype(np.float32)
+    wp, bd = _dev(_pack(w), "bf16"), _dev(b)
+
+    def run(k, wd=W):
+        return ops.conv(_dev(x0[:k, :, :wd], "bf16"), wp, cout, ks, stride, up,
+                        x1=_dev(x1[:k, :, :wd], "bf16") if c1 else None, bias=bd).float().cpu().numpy()
+
+    full = run(n)
+    if n > 1:
+        assert np.array_equal(full[:1], run(1))
+    elif ks == 1:
+        assert np.array_equal(full[:, :, :min(W, 100)], run(1, min(W, 100)))
+    i = n - 1
+    wd = W if ks == 3 else min(W, 500)  # (the last columns of a linear's row)
+    a = x0[i].astype(np.float64) if not c1 else np.concatenate([x0[i], x1[i]], axis=2).astype(np.float64)
+    a = a[:, W - wd:]
+    ref = O.conv2d(O.upsample_nearest2x(a) if up else a, w, b, stride)
+    err = rel_l2(full[i][:, full.shape[2] - ref.shape[1]:], ref)
+    assert err <= TOL["bf16"], err
+
+
 OUT_CASES = [
     # n_req, cfg flags, H, W, C, in place, eps_out
     (3, (1, 0, 1), 12, 10, 64, False, True),     # one ragged tile (120 pixels)
