@@ -28,7 +28,7 @@
 //    probability exceeds 2^8); the rescale of the accumulators, the rare
 //    case after the first tile, is a wave-uniform branch.  The result is
 //    the same softmax: any m with no overflow gives the same quotient.
-// fp32: one thread per query, K/V tiles in LDS, fp32 online softmax.
+// fp32: K/V tiles in LDS, fp32 online softmax, 16 lanes or one thread per query.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -550,6 +550,108 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
   }
 }
 
+// fp32, heads up to 64 wide: 16 lanes per query, each over the keys of its
+// residue mod 16 with its own online softmax (four keys of a 64-key LDS tile
+// at a time), merged at the end, so that a query's chain is Nk / 64 tiles of
+// four keys instead of Nk keys: 256 queries x 256 keys, 4 heads of 8, 3 images
+// 272 -> 15 us.  (A thread per query left 48 waves on the chip.)
+template <int DMAX>
+__global__ __launch_bounds__(256) void attn_f32_lanes_kernel(AttnArgs a) {
+  constexpr int KTF = 64, LQ = 16, QB = 256 / LQ, KL = KTF / LQ, LD = DMAX + 4;
+  __shared__ __attribute__((aligned(16))) float Ks[KTF * LD];
+  __shared__ __attribute__((aligned(16))) float Vs[KTF * LD];
+  const int tid = threadIdx.x, part = tid & (LQ - 1);
+  const int img = blockIdx.z, head = blockIdx.y;
+  const int q = blockIdx.x * QB + tid / LQ;
+  const int kvimg = a.kv_index ? a.kv_index[img] : img;
+  const int hd = head * a.d, d = a.d;
+  const float* Q = reinterpret_cast<const float*>(a.q) + (long)img * a.q_img + hd;
+  const float* K = reinterpret_cast<const float*>(a.k) + (long)kvimg * a.k_img + hd;
+  const float* V = reinterpret_cast<const float*>(a.v) + (long)kvimg * a.v_img + hd;
+  // q_log2: Q holds q * scale * log2(e), so a score is a base-2 exponent
+  const bool l2 = a.q_log2 != 0;
+  float qv[DMAX], o[DMAX];
+#pragma unroll
+  for (int i = 0; i < DMAX; ++i) {
+    qv[i] = (q < a.Nq && i < d) ? Q[(long)q * a.q_ld + i] : 0.f;
+    o[i] = 0.f;
+  }
+  float m = -INFINITY, l = 0.f;
+  for (int k0 = 0; k0 < a.Nk; k0 += KTF) {
+    const int nk = min(KTF, a.Nk - k0);
+    __syncthreads();
+    for (int idx = tid; idx < KTF * DMAX; idx += 256) {
+      const int key = idx / DMAX, i = idx % DMAX;
+      const bool in = key < nk && i < d;
+      Ks[key * LD + i] = in ? K[(long)(k0 + key) * a.k_ld + i] : 0.f;
+      Vs[key * LD + i] = in ? V[(long)(k0 + key) * a.v_ld + i] : 0.f;
+    }
+    __syncthreads();
+    float sc[KL], mt = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < KL; ++u) {
+      const int key = part + LQ * u;
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < DMAX; i += 4) {
+        const float4 kk = *reinterpret_cast<const float4*>(&Ks[key * LD + i]);
+        s = fmaf(qv[i], kk.x, s);
+        s = fmaf(qv[i + 1], kk.y, s);
+        s = fmaf(qv[i + 2], kk.z, s);
+        s = fmaf(qv[i + 3], kk.w, s);
+      }
+      if (!l2) s *= a.scale;
+      sc[u] = key < nk ? s : -INFINITY;
+      mt = fmaxf(mt, sc[u]);
+    }
+    if (part < nk) {  // (a lane without a key in this tile keeps its state)
+      const float mn = fmaxf(m, mt);
+      const float al = l2 ? exp2f(m - mn) : expf(m - mn);
+      l *= al;
+#pragma unroll
+      for (int i = 0; i < DMAX; ++i) o[i] *= al;
+#pragma unroll
+      for (int u = 0; u < KL; ++u) {
+        const int key = part + LQ * u;
+        const float p = l2 ? exp2f(sc[u] - mn) : expf(sc[u] - mn);
+        l += p;
+#pragma unroll
+        for (int i = 0; i < DMAX; i += 4) {
+          const float4 vv = *reinterpret_cast<const float4*>(&Vs[key * LD + i]);
+          o[i] = fmaf(p, vv.x, o[i]);
+          o[i + 1] = fmaf(p, vv.y, o[i + 1]);
+          o[i + 2] = fmaf(p, vv.z, o[i + 2]);
+          o[i + 3] = fmaf(p, vv.w, o[i + 3]);
+        }
+      }
+      m = mn;
+    }
+  }
+  // merge the 16 lanes of the query (a lane that saw no key has m = -inf, l = 0)
+#pragma unroll
+  for (int off = LQ / 2; off > 0; off >>= 1) {
+    const float m2 = __shfl_xor(m, off, 64), l2s = __shfl_xor(l, off, 64);
+    const float mn = fmaxf(m, m2);
+    const float f1 = m > -INFINITY ? (l2 ? exp2f(m - mn) : expf(m - mn)) : 0.f;
+    const float f2 = m2 > -INFINITY ? (l2 ? exp2f(m2 - mn) : expf(m2 - mn)) : 0.f;
+    l = l * f1 + l2s * f2;
+#pragma unroll
+    for (int i = 0; i < DMAX; ++i) {
+      const float o2 = __shfl_xor(o[i], off, 64);
+      o[i] = o[i] * f1 + o2 * f2;
+    }
+    m = mn;
+  }
+  if (q < a.Nq) {
+    float* O = reinterpret_cast<float*>(a.o) + (long)img * a.o_img + (long)q * a.o_ld + hd;
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int i = 0; i < DMAX; ++i)
+      if (i < d && (i & (LQ - 1)) == part) O[i] = o[i] * inv;
+  }
+}
+
+// fp32, wider heads: one thread per query.
 template <int DMAX, int KTF>
 __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
   __shared__ float Ks[KTF * DMAX];
@@ -658,13 +760,17 @@ hipError_t launch_attention(DType dt, const AttnArgs& a, hipStream_t s) {
     }
   } else {
     if (a.vt || a.d <= 0) return hipErrorInvalidValue;
-    dim3 grid((a.Nq + 63) / 64, a.heads, a.imgs);
+    dim3 grid((a.Nq + 63) / 64, a.heads, a.imgs), lgrid((a.Nq + 15) / 16, a.heads, a.imgs);
     // (the wide heads keep q and o in scratch: the fp32 path is the
     // reference-precision path for small configurations, not a fast one)
-    if (a.d <= 16)
-      attn_f32_kernel<16, 64><<<grid, 64, 0, s>>>(a);
+    if (a.d <= 8)
+      attn_f32_lanes_kernel<8><<<lgrid, 256, 0, s>>>(a);
+    else if (a.d <= 16)
+      attn_f32_lanes_kernel<16><<<lgrid, 256, 0, s>>>(a);
+    else if (a.d <= 32)
+      attn_f32_lanes_kernel<32><<<lgrid, 256, 0, s>>>(a);
     else if (a.d <= 64)
-      attn_f32_kernel<64, 64><<<grid, 64, 0, s>>>(a);
+      attn_f32_lanes_kernel<64><<<lgrid, 256, 0, s>>>(a);
     else if (a.d <= 128)
       attn_f32_kernel<128, 32><<<grid, 64, 0, s>>>(a);
     else if (a.d <= 256)

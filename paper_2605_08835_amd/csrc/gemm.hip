@@ -4,7 +4,7 @@
 // activations (3x3 / 1x1 taps, stride 2, nearest-2x upsampling, two-source
 // channel concat, fused GroupNorm affine + SiLU) and B is the packed weight
 // matrix stored N-major with K contiguous.  bf16 runs on MFMA
-// (v_mfma_f32_32x32x16_bf16, fp32 accumulation); fp32 runs a SIMT FMA kernel
+// (v_mfma_f32_32x32x16_bf16, fp32 accumulation); fp32 on v_mfma_f32_16x16x4_f32
 // (true fp32, no reduced-precision products).
 #include "device_common.h"
 #include "kernels.h"
@@ -1110,77 +1110,122 @@ __global__ void splitk_reduce_kernel(GemmArgs a) {
   epilogue4<bf16>(a.epi, m, n, x);
 }
 
-// ---------------------------------------------------------------- fp32 SIMT
-namespace sf {
-constexpr int BM = 64, BN = 64, BK = 16;
+// ---------------------------------------------------------------- fp32 MFMA
+// v_mfma_f32_16x16x4_f32: fp32 products and sums.  The fp32 path runs narrow
+// layers (the test UNet: 192-768 rows, 4-512 columns, K 32-1152) whose time is
+// latency, so a block is one (16 T) x (16 T) output tile with K split over its
+// NW waves in 16-deep chunks (wave w takes chunks w, w + NW, ...).  A lane
+// loads four consecutive k of its row or column straight into the registers
+// the products read (lane l: row l % 16, k 4 (l / 16) .. + 3; element j of
+// every lane is MFMA j's k slice), four chunks in flight, no LDS and no barrier
+// until the NW partial tiles are added in wave order.  The chunks a wave
+// takes and the order of the sums depend on K alone, so a row's bits do not
+// depend on the tile or on its batch-mates.  Against 64x64 SIMT tiles with a
+// barrier every 16 k (event to event, some 5 us of it the launch): 192 x 64 x
+// 576 50 -> 8.9 us, 192 x 64 x 1152 93 -> 11.4 us, 768 x 32 x 32 10.5 -> 6.5 us.
+template <typename T4>
+__device__ __forceinline__ void a_quad(const ASeg& s, const RowPos& r, int k, float inv_cin, T4& v) {
+  v = T4{0.f, 0.f, 0.f, 0.f};
+  // k / cin by a float quotient corrected by one (exact below 2^24)
+  int tap = (int)((float)k * inv_cin), c = k - tap * s.cin;
+  if (c < 0) {
+    --tap;
+    c += s.cin;
+  } else if (c >= s.cin) {
+    ++tap;
+    c -= s.cin;
+  }
+  const float* p = a_chunk_ptr<float>(s, r, tap, c);
+  if (!p) return;
+  v = *reinterpret_cast<const T4*>(p);
+  if (s.scale) {
+    const T4 sc = *reinterpret_cast<const T4*>(s.scale + (long)r.img * s.cin + c);
+    const T4 sh = *reinterpret_cast<const T4*>(s.shift + (long)r.img * s.cin + c);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = v[i] * sc[i] + sh[i];
+      if (s.silu) v[i] = silu_f(v[i]);
+    }
+  }
 }
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  using namespace sf;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int tiles_n = (a.N + BN - 1) / BN;
+template <int T, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmArgs a) {
+  constexpr int BT = 16 * T, U = 4;  // tile edge; chunks in flight
+  __shared__ float part[NW][BT * BT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles_n = (a.N + BT - 1) / BT;
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const bool loads_a = tid < 128;
-  const int lrow = (tid & 127) >> 1, kc = tid & 1;
-  const RowPos rp = decode_row(a.seg[0], m0 + lrow, a.M);
-  const float* B = reinterpret_cast<const float*>(a.B);
-
-  float acc[4][4] = {};
-  const int nk = (a.K + BK - 1) / BK;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int k = kt * BK + kc * 8;
-    float v[8];
-    if (loads_a) {
-      if (k < a.seg[0].K) {
-        const int tap = k / a.seg[0].cin, c = k - tap * a.seg[0].cin;
-        a_chunk<float>(a.seg[0], rp, tap, c, v);
-      } else if (k < a.K) {
-        const int kk = k - a.seg[0].K;
-        const int tap = kk / a.seg[1].cin, c = kk - tap * a.seg[1].cin;
-        a_chunk<float>(a.seg[1], rp, tap, c, v);
-      } else {
+  const int m0 = tm * BT, n0 = tn * BT, lr = lane & 15, lk = 4 * (lane >> 4);
+  RowPos rp[T];
+  const float* bp[T];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) As[kc * 8 + i][lrow] = v[i];
-    } else {
-      const int n = n0 + lrow;
-      if (n < a.N && k < a.K) {
-        load8f(B + (long)n * a.ldb + k, v);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) Bs[kc * 8 + i][lrow] = v[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int t = 0; t < T; ++t) {
+    rp[t] = decode_row(a.seg[0], m0 + 16 * t + lr, a.M);
+    const int n = n0 + 16 * t + lr;
+    bp[t] = n < a.N ? reinterpret_cast<const float*>(a.B) + (long)n * a.ldb : nullptr;
   }
+  const int K0 = a.seg[0].K;
+  const float inv0 = 1.0f / (float)a.seg[0].cin, inv1 = a.seg[1].K ? 1.0f / (float)a.seg[1].cin : 0.f;
+  f32x4 acc[T][T];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-      if (row < a.M && col < a.N) epilogue_store<float>(a.epi, row, col, acc[i][j]);
+    for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 16 * wave; k0 < a.K; k0 += 16 * NW * U) {
+    f32x4 av[U][T], bv[U][T];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 16 * NW * u + lk;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        av[u][t] = bv[u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (k < a.K) {
+          if (k < K0)
+            a_quad(a.seg[0], rp[t], k, inv0, av[u][t]);
+          else
+            a_quad(a.seg[1], rp[t], k - K0, inv1, av[u][t]);
+          if (bp[t]) bv[u][t] = *reinterpret_cast<const f32x4*>(bp[t] + k);
+        }
+      }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < T; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][j][e], acc[i][j], 0, 0, 0);
+  }
+  // lane l holds rows 4 (l / 16) + r, column l % 16 of each 16x16 tile
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave][(16 * i + lk + r) * BT + 16 * j + lr] = acc[i][j][r];
+  __syncthreads();
+  for (int o = tid; o < BT * BT; o += 64 * NW) {
+    float v = part[0][o];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += part[w][o];
+    const int row = m0 + o / BT, col = n0 + o % BT;
+    if (row < a.M && col < a.N) epilogue_store<float>(a.epi, row, col, v);
+  }
+}
+
+// K split over 8 waves from K = 256 on, else 4 or 2 (a function of K alone);
+// 32x32 tiles (half the operand traffic) once 16x16 ones would give the chip
+// over four blocks per CU.
+template <int NW>
+static void launch_f32(const GemmArgs& a, hipStream_t s) {
+  auto blocks = [&](long bt) { return ((a.M + bt - 1) / bt) * ((a.N + bt - 1) / bt); };
+  if (blocks(16) > 1024)
+    gemm_f32_kernel<2, NW><<<dim3((unsigned)blocks(32)), dim3(64 * NW), 0, s>>>(a);
+  else
+    gemm_f32_kernel<1, NW><<<dim3((unsigned)blocks(16)), dim3(64 * NW), 0, s>>>(a);
 }
 
 static bool fast_seg(const ASeg& g, int Ho, int Wo, int BK) {
@@ -1370,8 +1415,12 @@ hipError_t launch_gemm(DType dt, const GemmArgs& args, hipStream_t s) {
       launch_bf16<256, 32, 64, 4, 1>(a, s);
     }
   } else {
-    const long blocks = (long)((a.M + sf::BM - 1) / sf::BM) * ((a.N + sf::BN - 1) / sf::BN);
-    gemm_f32_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(a);
+    if (a.K >= 256)
+      launch_f32<8>(a, s);
+    else if (a.K > 64)
+      launch_f32<4>(a, s);
+    else
+      launch_f32<2>(a, s);
   }
   return hipGetLastError();
 }

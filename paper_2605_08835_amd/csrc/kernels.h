@@ -104,7 +104,7 @@ size_t groupnorm_partial_floats(int imgs, int hw, int cin);
 size_t groupnorm_scratch_floats_max();
 hipError_t groupnorm_scratch(float** out);
 // out = act(x * scale + shift) over the concat [src0 | src1] (act = SiLU or identity).
-// Statistics and apply in one launch for small images (bf16; see
+// Statistics and apply in one launch for small images (see
 // groupnorm_fused_ok for the shapes it takes).
 bool groupnorm_fused_ok(DType dt, int c0, int c1, int hw, int groups);
 hipError_t launch_groupnorm_fused(DType dt, const void* src0, int c0, const void* src1, int c1, int imgs, int hw,

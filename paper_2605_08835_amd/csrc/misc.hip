@@ -451,15 +451,16 @@ hipError_t launch_groupnorm_apply(DType dt, const void* src0, int c0, const void
 // the block, and writes act(x * scale + shift) with the same per-channel
 // scale and shift as the three-pass form.  One launch instead of three, and
 // one read of the input.
-template <int W> struct bvec;
-template <> struct bvec<4> { typedef bf16x4 type; };
-template <> struct bvec<8> { typedef bf16x8 type; };
+template <typename T, int W> struct bvec;
+template <> struct bvec<bf16, 4> { typedef bf16x4 type; };
+template <> struct bvec<bf16, 8> { typedef bf16x8 type; };
+template <> struct bvec<float, 4> { typedef f32x4 type; };
 
-template <int E, int W>
-__global__ __launch_bounds__(256) void gn_fused_kernel(const bf16* src0, int c0, const bf16* src1, int c1,
+template <typename T, int E, int W>
+__global__ __launch_bounds__(256) void gn_fused_kernel(const T* src0, int c0, const T* src1, int c1,
                                                        int hw, int groups, float eps, const float* gamma,
-                                                       const float* beta, int silu, bf16* out) {
-  typedef typename bvec<W>::type vec;
+                                                       const float* beta, int silu, T* out) {
+  typedef typename bvec<T, W>::type vec;
   const int g = blockIdx.x, img = blockIdx.y, tid = threadIdx.x;
   const int cin = c0 + c1, cpg = cin / groups, V = cpg / W, n = hw * V, cg = g * cpg;
   float v[E][W];
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(256) void gn_fused_kernel(const bf16* src0, int c0,
     const int i = tid + 256 * e;
     if (i < n) {
       const int p = i / V, c = cg + (i - p * V) * W;
-      const bf16* src = c < c0 ? src0 + ((long)img * hw + p) * c0 + c : src1 + ((long)img * hw + p) * c1 + (c - c0);
+      const T* src = c < c0 ? src0 + ((long)img * hw + p) * c0 + c : src1 + ((long)img * hw + p) * c1 + (c - c0);
       const vec a = *reinterpret_cast<const vec*>(src);
 #pragma unroll
       for (int k = 0; k < W; ++k) {
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(256) void gn_fused_kernel(const bf16* src0, int c0,
         const float sc = gamma[c + k] * rstd;
         float y = v[e][k] * sc + (beta[c + k] - (float)mean * sc);
         if (silu) y = silu_f(y);
-        o[k] = (bf16)y;
+        o[k] = (T)y;
       }
       *reinterpret_cast<vec*>(out + ((long)img * hw + p) * cin + c) = o;
     }
@@ -513,7 +514,7 @@ __global__ __launch_bounds__(256) void gn_fused_kernel(const bf16* src0, int c0,
 
 bool groupnorm_fused_ok(DType dt, int c0, int c1, int hw, int groups) {
   const int cin = c0 + c1;
-  if (dt != BF16 || groups <= 0 || cin % groups || c0 % 4 || c1 % 4) return false;
+  if (groups <= 0 || cin % groups || c0 % 4 || c1 % 4) return false;
   const int cpg = cin / groups;
   return cpg % 4 == 0 && (long)hw * (cpg / 4) <= 256L * 20;
 }
@@ -525,24 +526,34 @@ hipError_t launch_groupnorm_fused(DType dt, const void* src0, int c0, const void
   if (imgs == 0 || hw == 0) return hipSuccess;
   const int cpg = (c0 + c1) / groups;
   const dim3 grid(groups, imgs);
+  if (dt == F32) {  // vectors of 4 channels (16 bytes)
+    const float *a = (const float*)src0, *b = (const float*)src1;
+    float* o = (float*)out;
+    const long n = (long)hw * (cpg / 4);  // <= 5120
+    if (n <= 256 * 4)
+      gn_fused_kernel<float, 4, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+    else
+      gn_fused_kernel<float, 20, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+    return hipGetLastError();
+  }
   const bf16 *a = (const bf16*)src0, *b = (const bf16*)src1;
   bf16* o = (bf16*)out;
   if (cpg % 8 == 0 && c0 % 8 == 0 && c1 % 8 == 0) {
     const long n = (long)hw * (cpg / 8);  // <= 2560
     if (n <= 256 * 4)
-      gn_fused_kernel<4, 8><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+      gn_fused_kernel<bf16, 4, 8><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
     else if (n <= 256 * 8)
-      gn_fused_kernel<8, 8><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+      gn_fused_kernel<bf16, 8, 8><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
     else
-      gn_fused_kernel<10, 8><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+      gn_fused_kernel<bf16, 10, 8><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
   } else {
     const long n = (long)hw * (cpg / 4);  // <= 5120
     if (n <= 256 * 4)
-      gn_fused_kernel<4, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+      gn_fused_kernel<bf16, 4, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
     else if (n <= 256 * 8)
-      gn_fused_kernel<8, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+      gn_fused_kernel<bf16, 8, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
     else
-      gn_fused_kernel<20, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
+      gn_fused_kernel<bf16, 20, 4><<<grid, 256, 0, s>>>(a, c0, b, c1, hw, groups, eps, gamma, beta, silu, o);
   }
   return hipGetLastError();
 }

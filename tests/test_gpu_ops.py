@@ -465,6 +465,32 @@ def test_conv_tiles64(ops, case):
     assert err <= TOL["bf16"], err
 
 
+# rows, K, N: one partial K chunk, the edges of the 2 / 4 / 8-wave splits (K 64,
+# 72, 248, 256), a chunk count that is no multiple of the waves, ragged 16x16
+# tiles; the last two take 32x32 tiles (over 1024 tiles of 16x16).
+F32_LINEAR_CASES = [(1, 8, 4), (17, 64, 16), (33, 72, 20), (40, 248, 36), (16, 256, 64), (5, 1032, 12),
+                    (4113, 40, 68), (8200, 264, 40)]
+
+
+@pytest.mark.parametrize("case", F32_LINEAR_CASES)
+def test_linear_f32(ops, case):
+    """The fp32 GEMM against float64, and a row's bits whatever the row count."""
+    M, K, N = case
+    log(f"linear f32 {case}")
+    rng = np.random.default_rng(M + K + N)
+    x, w = _vals(rng, (1, 1, M, K), "f32"), _vals(rng, (N, K), "f32", 1.0 / math.sqrt(K))
+    b, r = rng.standard_normal(N).astype(np.float32), _vals(rng, (1, 1, M, N), "f32")
+    k = min(M, 19)
+
+    def run(m):
+        return ops.conv(_dev(x[:, :, :m]), _dev(w), N, ks=1, bias=_dev(b), resid=_dev(r[:, :, :m])).cpu().numpy()[0, 0]
+
+    full = run(M)
+    assert np.array_equal(full[:k], run(k))
+    ref = x[0, 0].astype(np.float64) @ w.astype(np.float64).T + b + r[0, 0]
+    assert rel_l2(full, ref) <= TOL["f32"]
+
+
 OUT_CASES = [
     # n_req, cfg flags, H, W, C, in place, eps_out
     (3, (1, 0, 1), 12, 10, 64, False, True),     # one ragged tile (120 pixels)
