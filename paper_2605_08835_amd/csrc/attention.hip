@@ -79,81 +79,80 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 __device__ inline bf16x8 ld16(const bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
-// Online-softmax step on one 64-key tile of S^T (NKT = 2), or on its first
-// 32 keys (NKT = 1: a last tile of at most 32 keys).  On entry s holds the raw
-// products: base-2 logits minus m when MF, base-2 logits when QS, plain
-// q.k otherwise.  Moves m where the tile exceeds it by more than TAU,
-// rescales the accumulators then, and leaves P = exp2(logit - m) in s.  SF:
-// the row sum comes out of the PV product, else it is added up here.
-template <int NJ, int ND, bool QS, bool MF, bool SF, bool TAIL, int NKT = 2>
-__device__ __forceinline__ void softmax_tile(f32x16 (&s)[2], f32x16 (&o)[ND], bf16x8 (&qf)[NJ], float& m_run,
-                                             float& l_run, bool first, int kvalid, int lh, int d, float sl2) {
+// First half of the online-softmax step on one 64-key tile of S^T (NKT = 2),
+// or on its first 32 keys (NKT = 1: a last tile of at most 32 keys), for QG
+// query groups.  On entry s holds the raw products: base-2 logits minus m when
+// MF, base-2 logits when QS, plain q.k otherwise.  Moves m where the tile
+// exceeds it by more than TAU, rescales the accumulators then, and leaves the
+// logits minus m in s (the exp2 follows beside the PV products).  One branch
+// serves all groups: where a lane's m stays, the rescale multiplies by one.
+template <int QG, int NJ, int ND, bool QS, bool MF, bool TAIL, int NKT = 2>
+__device__ __forceinline__ void softmax_max(f32x16 (&s)[QG][2], f32x16 (&o)[QG][ND], bf16x8 (&qf)[QG][NJ],
+                                            float (&m_run)[QG], float (&l_run)[QG], bool first, int kvalid, int lh,
+                                            int d, float sl2) {
   using namespace fa;
-  if constexpr (!QS) {
+  float mt[QG];
+  bool need[QG], any = false;
 #pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
+  for (int g = 0; g < QG; ++g) {
+    if constexpr (!QS) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[kt][r] = fmaf(s[kt][r], sl2, -m_run);
-  } else if constexpr (!MF) {  // no spare column: subtract m here
+      for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
+        for (int r = 0; r < 16; ++r) s[g][kt][r] = fmaf(s[g][kt][r], sl2, -m_run[g]);
+    } else if constexpr (!MF) {  // no spare column: subtract m here
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[kt][r] -= m_run;
-  }
-  if constexpr (TAIL) {  // keys at or past kvalid; compared as immediates against one register
-    const int lim = kvalid - 4 * lh;
-    static_for<0, 16 * NKT>([&](auto I) {
-      constexpr int kt = I.value / 16, r = I.value % 16;
-      if (kt * 32 + 8 * (r >> 2) + (r & 3) >= lim) s[kt][r] = -1e30f;
-    });
-  }
-  float mt = -1e30f;
+      for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-  for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[kt][r]);
-  mt = xor32_max(mt);
-  const bool need = first || mt > TAU;
-  if (__any(need)) {
-    // move m to the (bf16-rounded) tile maximum where needed
-    float delta = 0.f;
-    if (need) {
-      const float mn = bf16_rne(m_run + mt);
-      delta = mn - m_run;
-      m_run = mn;
+        for (int r = 0; r < 16; ++r) s[g][kt][r] -= m_run[g];
     }
-    // (nothing has accumulated before the first tile; its delta may be any
-    // size, so alpha is not evaluated there)
-    const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-delta);
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kt][r] -= delta;
-    l_run *= alpha;
-#pragma unroll
-    for (int t = 0; t < ND; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
-    if constexpr (MF) {
-      const bf16 nm = (bf16)(-m_run);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (16 * j + 8 * lh + e == d) qf[j][e] = nm;
+    if constexpr (TAIL) {  // keys at or past kvalid; compared as immediates against one register
+      const int lim = kvalid - 4 * lh;
+      static_for<0, 16 * NKT>([&](auto I) {
+        constexpr int kt = I.value / 16, r = I.value % 16;
+        if (kt * 32 + 8 * (r >> 2) + (r & 3) >= lim) s[g][kt][r] = -1e30f;
+      });
     }
-  }
-#pragma unroll
-  for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[kt][r] = __builtin_amdgcn_exp2f(s[kt][r]);
-  if constexpr (!SF) {
-    float ps = 0.f;
+    mt[g] = -1e30f;
 #pragma unroll
     for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ps += s[kt][r];
-    l_run += ps;
+      for (int r = 0; r < 16; ++r) mt[g] = fmaxf(mt[g], s[g][kt][r]);
+    mt[g] = xor32_max(mt[g]);
+    need[g] = first || mt[g] > TAU;
+    any = any || need[g];
+  }
+  if (__any(any)) {
+#pragma unroll
+    for (int g = 0; g < QG; ++g) {
+      // move m to the (bf16-rounded) tile maximum where needed
+      float delta = 0.f;
+      if (need[g]) {
+        const float mn = bf16_rne(m_run[g] + mt[g]);
+        delta = mn - m_run[g];
+        m_run[g] = mn;
+      }
+      // (nothing has accumulated before the first tile; its delta may be any
+      // size, so alpha is not evaluated there)
+      const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-delta);
+#pragma unroll
+      for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[g][kt][r] -= delta;
+      l_run[g] *= alpha;
+#pragma unroll
+      for (int t = 0; t < ND; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[g][t][r] *= alpha;
+      if constexpr (MF) {
+        const bf16 nm = (bf16)(-m_run[g]);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (16 * j + 8 * lh + e == d) qf[g][j][e] = nm;
+      }
+    }
   }
 }
 
@@ -438,31 +437,53 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
 #pragma unroll
         for (int g = 0; g < QG; ++g) s[g][kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[g][j], s[g][kt], 0, 0, 0);
       }
-#pragma unroll
-    for (int g = 0; g < QG; ++g)
-      softmax_tile<NJ, ND, QS, MF, SF, TAIL, NKT>(s[g], o[g], qf[g], m_run[g], l_run[g], it == 0, a.Nk - k0, lh, d,
-                                                  sl2);
+    softmax_max<QG, NJ, ND, QS, MF, TAIL, NKT>(s, o, qf, m_run, l_run, it == 0, a.Nk - k0, lh, d, sl2);
 
     // O^T += V^T P^T over four 16-key slices.  Slot (lh, i) of slice u is
     // key 16u + 8(i/4) + 4 lh + i%4, i.e. register 8(u%2) + i of S^T tile u/2.
+    // The steps (slice, group) run one behind the exp2s, so the products of a
+    // step and the probabilities of the next can issue side by side (2 rows,
+    // 4096 tokens, d = 40: 77 -> 70 us; 12 rows 336 -> 332 us, where the
+    // exp2s, a quarter of the plain rate, take most of the vector units' time).
+    constexpr int NS = 2 * NKT * QG;  // steps: slice u = step / QG, group step % QG
+    bf16x8 pf[2], vf[2][ND];
+    float ps[QG];
 #pragma unroll
-    for (int u = 0; u < 2 * NKT; ++u) {
-      bf16x8 pf[QG];
+    for (int g = 0; g < QG; ++g) ps[g] = 0.f;
+    auto prob = [&](auto ST) __attribute__((always_inline)) {
+      constexpr int g = ST.value % QG, u = ST.value / QG;
 #pragma unroll
-      for (int g = 0; g < QG; ++g)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) pf[g][i] = (bf16)s[g][u >> 1][8 * (u & 1) + i];
+      for (int i = 0; i < 8; ++i) {
+        const float p = __builtin_amdgcn_exp2f(s[g][u >> 1][8 * (u & 1) + i]);
+        if constexpr (!SF) ps[g] += p;  // SF: the row sum comes out of the PV product
+        pf[ST.value & 1][i] = (bf16)p;
+      }
+    };
+    auto vload = [&](auto UU) __attribute__((always_inline)) {
+      constexpr int u = UU.value;
 #pragma unroll
       for (int t = 0; t < ND; ++t) {
         const bf16* vrow = &Vb[(t * 32 + lq) * LDV + 16 * u + 4 * lh];
         const bf16x4 lo = *reinterpret_cast<const bf16x4*>(vrow);
         const bf16x4 hi = *reinterpret_cast<const bf16x4*>(vrow + 8);
-        bf16x8 vf;
-        vf[0] = lo[0]; vf[1] = lo[1]; vf[2] = lo[2]; vf[3] = lo[3];
-        vf[4] = hi[0]; vf[5] = hi[1]; vf[6] = hi[2]; vf[7] = hi[3];
-#pragma unroll
-        for (int g = 0; g < QG; ++g) o[g][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[g], o[g][t], 0, 0, 0);
+        bf16x8& v = vf[u & 1][t];
+        v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3];
+        v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
       }
+    };
+    vload(IC<0>{});
+    prob(IC<0>{});
+    static_for<0, NS>([&](auto ST) {
+      constexpr int g = ST.value % QG, u = ST.value / QG;
+      if constexpr (g == QG - 1 && u + 1 < 2 * NKT) vload(IC<u + 1>{});
+      if constexpr (ST.value + 1 < NS) prob(IC<ST.value + 1>{});
+#pragma unroll
+      for (int t = 0; t < ND; ++t)
+        o[g][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u & 1][t], pf[ST.value & 1], o[g][t], 0, 0, 0);
+    });
+    if constexpr (!SF) {
+#pragma unroll
+      for (int g = 0; g < QG; ++g) l_run[g] += ps[g];
     }
     if constexpr (FULL && PF2) {
       // The next tile's data was fetched a tile ago; of the loads issued
@@ -518,7 +539,12 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
   }
 
   // O^T accumulator: lane holds head dims t*32 + 8(r/4) + 4 lh + [0, 4) of
-  // its query; each run of 4 is one 8-byte store.
+  // its query.  Each wave lays its queries' rows out in LDS (the K tiles are
+  // done with: every tile ends with a barrier) and stores them row-contiguous,
+  // 16 bytes per lane, instead of 8-byte pieces of 32 rows at a time.
+  static_assert(NW * 32 * LDK <= 2 * KT * LDK, "the waves' rows fit the K tiles");
+  bf16* R = &Ks[0][0] + wave * 32 * LDK;
+  const int d8 = FAST ? DV / 8 : d >> 3;
 #pragma unroll
   for (int g = 0; g < QG; ++g) {
     float l = l_run[g];
@@ -531,22 +557,27 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
           if (32 * t + 8 * (r >> 2) + 4 * lh + (r & 3) == d) l = o[g][t][r];
     }
     const float inv = 1.0f / xor32_sum(l);
-    const int q = qb + 32 * g + lq;
-    if (q < a.Nq) {
-      bf16* O = reinterpret_cast<bf16*>(a.o) + (long)img * a.o_img + (long)q * a.o_ld + hd;
 #pragma unroll
-      for (int t = 0; t < ND; ++t)
+    for (int t = 0; t < ND; ++t)
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int dd = t * 32 + 8 * rg + 4 * lh;
-          if (dd < d) {
-            bf16x4 w;
+      for (int rg = 0; rg < 4; ++rg) {
+        const int dd = t * 32 + 8 * rg + 4 * lh;
+        if (dd < d) {
+          bf16x4 w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[g][t][4 * rg + e] * inv);
-            *reinterpret_cast<bf16x4*>(O + dd) = w;
-          }
+          for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[g][t][4 * rg + e] * inv);
+          *reinterpret_cast<bf16x4*>(R + lq * LDK + dd) = w;
         }
+      }
+    asm volatile("" ::: "memory");  // (one wave's LDS accesses complete in order)
+    bf16* O = reinterpret_cast<bf16*>(a.o) + (long)img * a.o_img + hd;
+    for (int c = lane; c < 32 * d8; c += 64) {
+      const int row = c / d8, ch = c - row * d8, q = qb + 32 * g + row;
+      if (q < a.Nq)
+        *reinterpret_cast<bf16x8*>(O + (long)q * a.o_ld + 8 * ch) =
+            *reinterpret_cast<const bf16x8*>(R + row * LDK + 8 * ch);
     }
+    asm volatile("" ::: "memory");
   }
 }
 

@@ -1345,6 +1345,13 @@ static int pick_tile64(long M, long N, long K, int ksplit) {
 
 static bool launch_tile64(const GemmArgs& a, hipStream_t s) {
   if (loader_mode(a, 64) == 0) return false;
+  // Short-K GEGLU projections are as long in their epilogue (some 25 vector
+  // instructions per output) as in their products, so two blocks per CU, one
+  // in each, beat the deeper stages: K = 320, 196608 x 2560 564 against 622 us,
+  // K = 640, 10240 x 5120 100 against 106 us (K = 1280 347 against 333).
+  if (a.epi.geglu && a.K <= 640 && (long)((a.M + 255) / 256) * (a.N / 160) >= 512 &&
+      launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s))
+    return true;
   switch (pick_tile64(a.M, a.N, a.K, a.ksplit)) {
     case 0: return launch_dma<64, 64, 2, 2, 64, 4, 2>(a, s);
     case 1: return launch_dma<128, 64, 2, 2, 64, 3, 2>(a, s);

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime_api.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 
 #include "kernels.h"
@@ -168,7 +169,7 @@ sd_status synerdiff_op_groupnorm_stats_noalloc(int32_t dtype, const void* x0, in
     return op_fail(SD_ERR_INVALID_ARG, "bad shape");
   if (cin > 4096) return op_fail(SD_ERR_UNSUPPORTED, "too many channels");
   if (n == 0) return SD_OK;
-  const size_t need = groupnorm_partial_floats(n, hw, cin);
+  const size_t need = groupnorm_noalloc_floats(n, hw, cin);
   if (need > groupnorm_scratch_floats_max()) {
     g_err = "groupnorm_stats_noalloc: " + std::to_string(need) + " partial floats exceed the library scratch of " +
             std::to_string(groupnorm_scratch_floats_max()) + " (use synerdiff_op_groupnorm_stats with a buffer)";
@@ -177,9 +178,20 @@ sd_status synerdiff_op_groupnorm_stats_noalloc(int32_t dtype, const void* x0, in
   float* part = nullptr;
   const sd_status st = op_hip(groupnorm_scratch(&part), "groupnorm scratch address");
   if (st != SD_OK) return st;
-  return op_hip(launch_groupnorm_stats((DType)dtype, x0, c0, x1, c1, n, hw, groups, eps, gamma, beta, part, scale,
-                                       shift, (hipStream_t)stream),
-                "groupnorm_noalloc");
+  // (passes over as many images as the scratch holds; one always fits)
+  const size_t esz = dtype == SD_BF16 ? 2 : 4;
+  const int per = (int)std::min<size_t>((size_t)n, groupnorm_scratch_floats_max() / groupnorm_partial_floats(1, hw, cin));
+  for (int i = 0; i < n; i += per) {
+    const int k = std::min(per, n - i);
+    const size_t px = (size_t)i * hw;
+    const sd_status e = op_hip(
+        launch_groupnorm_stats((DType)dtype, (const uint8_t*)x0 + px * c0 * esz, c0,
+                               c1 ? (const uint8_t*)x1 + px * c1 * esz : x1, c1, k, hw, groups, eps, gamma, beta, part,
+                               scale + (size_t)i * cin, shift + (size_t)i * cin, (hipStream_t)stream),
+        "groupnorm_noalloc");
+    if (e != SD_OK) return e;
+  }
+  return SD_OK;
 }
 
 sd_status synerdiff_op_groupnorm_fused(int32_t dtype, const void* x0, int32_t c0, const void* x1, int32_t c1,

@@ -227,10 +227,35 @@ def test_attention(ops, dt, qmode, heads, d, nq, nk, scale, cross):
         assert err <= tol, (i, err)
 
 
+@pytest.mark.parametrize("d,nq,nk", [(40, 129, 77), (64, 300, 64), (80, 33, 130), (160, 70, 90), (24, 5, 8)])
+def test_attention_strided_output(ops, d, nq, nk):
+    """Output rows wider than the heads (ragged last query block): the columns
+    and rows outside the result keep their values."""
+    heads, n = 2, 2
+    log(f"attention strided output d={d} nq={nq} nk={nk}")
+    rng = np.random.default_rng(d + nq)
+    C, pad = heads * d, 16
+    q, k, v = (_vals(rng, (n, t, C), "bf16") for t in (nq, nk, nk))
+    ld = (nk + 7) // 8 * 8
+    vdev = torch.zeros(n, C, ld, device="cuda", dtype=torch.bfloat16)
+    vdev[:, :, :nk] = _dev(v, "bf16").transpose(1, 2)
+    o = torch.full((n, nq + 3, C + pad), 7.0, device="cuda", dtype=torch.bfloat16)
+    ops.attention(_dev(q, "bf16"), _dev(k, "bf16"), vdev, o, n, heads, d, nq, nk, C, nq * C, C, nk * C, ld, C * ld,
+                  C + pad, (nq + 3) * (C + pad), 1.0 / math.sqrt(d), v_transposed=True)
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy()
+    assert (got[:, nq:] == 7.0).all() and (got[:, :, C:] == 7.0).all()
+    for i in range(n):
+        ref = O.attention(q[i].astype(np.float64), k[i].astype(np.float64), v[i].astype(np.float64), heads)
+        assert rel_l2(got[i, :nq, :C], ref) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("n,H,W,c0,c1,G,eps", [(2, 8, 8, 64, 0, 32, 1e-5), (2, 16, 12, 320, 0, 32, 1e-6),
                                                (3, 8, 8, 64, 32, 32, 1e-5), (2, 4, 4, 1280, 640, 32, 1e-5),
-                                               (2, 64, 64, 320, 0, 32, 1e-5), (1, 16, 16, 32, 32, 8, 1e-5)])
+                                               (2, 64, 64, 320, 0, 32, 1e-5), (1, 16, 16, 32, 32, 8, 1e-5),
+                                               # many pixel ranges (four-wave finalize; 256 at most, ragged)
+                                               (1, 301, 277, 128, 0, 32, 1e-6), (2, 130, 131, 256, 64, 32, 1e-6)])
 def test_groupnorm(ops, dt, n, H, W, c0, c1, G, eps):
     log(f"groupnorm {dt} {(n, H, W, c0, c1, G)}")
     rng = np.random.default_rng(c0 + c1 + H)
