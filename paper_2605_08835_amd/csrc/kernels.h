@@ -166,10 +166,9 @@ struct OutArgs {
   const float* req_coef;  // [n_req, 3] = (A, B, w)
   const int* order;
   int n_req, H, W, C;
-  int tiles;  // set by the launcher
+  int tiles, P;  // blocks per request, pixels per block: set by the launcher
 };
 bool out_cfg_ddim_ok(DType dt, int latent_c, int H, int W, int C);
-size_t out_cfg_ddim_lds_bytes(int W);
 hipError_t launch_out_cfg_ddim(const OutArgs& a, hipStream_t s);
 hipError_t launch_cfg_ddim(const float* eps_rows, const float* lat_in, float* lat_out,
                            float* eps_out, int n_req, int lc, int hw, const int* req_row_u,

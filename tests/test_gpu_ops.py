@@ -516,6 +516,27 @@ def test_linear_f32(ops, case):
     assert rel_l2(full, ref) <= TOL["f32"]
 
 
+@pytest.mark.parametrize("P", [64, 128, 256])
+def test_conv_out_cfg_ddim_splits(ops, P):
+    """The 8-wave form at 64, 128 and 256 pixels a block gives the bits of the
+    4-wave form (384 blocks of 256 pixels and more)."""
+    H, W, C, n = 18, 32, 64, 128  # 576 pixels: 9, 5 and 3 blocks a request, the last ones ragged
+    rng = np.random.default_rng(7)
+    few = {64: 28, 128: 50, 256: 127}[P]
+    x = _dev(_vals(rng, (2 * n, H, W, C), "bf16"), "bf16")
+    w, b = _dev(_vals(rng, (4, 36 * C // 4), "bf16", 0.05), "bf16"), _dev(rng.standard_normal(4).astype(np.float32))
+    ru = np.where(np.arange(n) % 3 == 1, -1, n + np.arange(n)).astype(np.int32)
+    coef = _dev(rng.uniform(0.5, 2.0, (n, 3)).astype(np.float32))
+    lat = _dev(rng.standard_normal((n, 4, H, W)).astype(np.float32))
+
+    def run(k):
+        out, eps = torch.empty_like(lat[:k]), torch.empty_like(lat[:k])
+        ops.conv_out_cfg_ddim(x, w, b, _dev(ru[:k]), coef[:k], lat[:k], out, eps)
+        return torch.stack((out, eps)).cpu()
+
+    assert torch.equal(run(few), run(n)[:, :few])
+
+
 OUT_CASES = [
     # n_req, cfg flags, H, W, C, in place, eps_out
     (3, (1, 0, 1), 12, 10, 64, False, True),     # one ragged tile (120 pixels)
