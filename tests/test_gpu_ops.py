@@ -516,6 +516,24 @@ def test_linear_f32(ops, case):
     assert rel_l2(full, ref) <= TOL["f32"]
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("K", [8, 1020, 1024, 1284, 2816])
+def test_linear_rows_few(ops, K, dt):
+    """Up to 8 rows (staged whole, 2 / 4 / 8 at a time; 2816 columns of 8 rows
+    exceed the stage) give the bits that the same rows have among 40."""
+    rng = np.random.default_rng(K)
+    N = 50
+    x, w = rng.standard_normal((40, K)).astype(np.float32), _vals(rng, (N, K), dt, 1.0 / math.sqrt(K))
+    b, add = rng.standard_normal(N).astype(np.float32), rng.standard_normal((40, N)).astype(np.float32)
+
+    def run(m):
+        return ops.linear_rows(_dev(x[:m]), _dev(w, dt), _dev(b), _dev(add[:m]), 1, 1).cpu().numpy()
+
+    full = run(40)
+    for m in (1, 2, 3, 4, 5, 8):
+        assert np.array_equal(run(m), full[:m]), m
+
+
 @pytest.mark.parametrize("P", [64, 128, 256])
 def test_conv_out_cfg_ddim_splits(ops, P):
     """The 8-wave form at 64, 128 and 256 pixels a block gives the bits of the
