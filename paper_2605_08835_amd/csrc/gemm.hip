@@ -91,18 +91,6 @@ __device__ inline bf16x8 a_chunk_bf16(const ASeg& s, const RowPos& r, int tap, i
   return v;
 }
 
-template <typename T>
-__device__ inline void epilogue_store(const Epi& e, int row, int col, float v) {
-  if (e.bias) v += e.bias[col];
-  if (e.tbias) v += e.tbias[(long)(row / e.hw) * e.tb_ld + e.tb_off + col];
-  if (e.resid) v += to_f(reinterpret_cast<const T*>(e.resid)[(long)row * e.ldr + col]);
-  if (col < e.qcols) v *= e.qscale;
-  if (e.out_f32)
-    reinterpret_cast<float*>(e.out)[(long)row * e.ldo + col] = v;
-  else
-    reinterpret_cast<T*>(e.out)[(long)row * e.ldo + col] = from_f<T>(v);
-}
-
 // Output row of GEMM row m (the upsample phases write every other pixel of
 // every other image row).
 __device__ inline long out_row(const Epi& e, int m) {
@@ -1165,6 +1153,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmArgs a) {
     const int n = n0 + 16 * t + lr;
     bp[t] = n < a.N ? reinterpret_cast<const float*>(a.B) + (long)n * a.ldb : nullptr;
   }
+  // the epilogue's operands are on their way while the products run
+  constexpr int OPT = (BT * BT + 64 * NW - 1) / (64 * NW);  // outputs per thread
+  float eb[OPT], et[OPT], er[OPT];
+#pragma unroll
+  for (int i = 0; i < OPT; ++i) {
+    const int o = tid + 64 * NW * i, row = m0 + o / BT, col = n0 + o % BT;
+    const bool in = o < BT * BT && row < a.M && col < a.N;
+    eb[i] = in && a.epi.bias ? a.epi.bias[col] : 0.f;
+    et[i] = in && a.epi.tbias ? a.epi.tbias[(long)(row / a.epi.hw) * a.epi.tb_ld + a.epi.tb_off + col] : 0.f;
+    er[i] = in && a.epi.resid ? reinterpret_cast<const float*>(a.epi.resid)[(long)row * a.epi.ldr + col] : 0.f;
+  }
   const int K0 = a.seg[0].K;
   const float inv0 = 1.0f / (float)a.seg[0].cin, inv1 = a.seg[1].K ? 1.0f / (float)a.seg[1].cin : 0.f;
   f32x4 acc[T][T];
@@ -1207,12 +1206,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) part[wave][(16 * i + lk + r) * BT + 16 * j + lr] = acc[i][j][r];
   __syncthreads();
-  for (int o = tid; o < BT * BT; o += 64 * NW) {
-    float v = part[0][o];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) v += part[w][o];
-    const int row = m0 + o / BT, col = n0 + o % BT;
-    if (row < a.M && col < a.N) epilogue_store<float>(a.epi, row, col, v);
+  for (int i = 0; i < OPT; ++i) {
+    const int o = tid + 64 * NW * i, row = m0 + o / BT, col = n0 + o % BT;
+    if (o < BT * BT && row < a.M && col < a.N) {
+      float v = part[0][o];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += part[w][o];
+      v = v + eb[i] + et[i] + er[i];
+      if (col < a.epi.qcols) v *= a.epi.qscale;
+      reinterpret_cast<float*>(a.epi.out)[(long)row * a.epi.ldo + col] = v;
+    }
   }
 }
 
