@@ -637,14 +637,18 @@ __global__ __launch_bounds__(256) void attn_f32_lanes_kernel(AttnArgs a) {
     }
     if (part < nk) {  // (a lane without a key in this tile keeps its state)
       const float mn = fmaxf(m, mt);
-      const float al = l2 ? exp2f(m - mn) : expf(m - mn);
+      // A lane whose keys so far all score -inf takes the exponents against 0
+      // (-inf minus -inf is NaN): its probabilities are 0, and its share drops
+      // out of the merge.
+      const float mr = mn == -INFINITY ? 0.f : mn;
+      const float al = l2 ? exp2f(m - mr) : expf(m - mr);
       l *= al;
 #pragma unroll
       for (int i = 0; i < DMAX; ++i) o[i] *= al;
 #pragma unroll
       for (int u = 0; u < KL; ++u) {
         const int key = part + LQ * u;
-        const float p = l2 ? exp2f(sc[u] - mn) : expf(sc[u] - mn);
+        const float p = l2 ? exp2f(sc[u] - mr) : expf(sc[u] - mr);
         l += p;
 #pragma unroll
         for (int i = 0; i < DMAX; i += 4) {
@@ -719,8 +723,8 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
       for (int i = 0; i < DMAX; ++i)
         if (i < d) sc = fmaf(qv[i], Ks[key * DMAX + i], sc);
       if (!l2) sc *= a.scale;
-      const float mn = fmaxf(m, sc);
-      const float al = l2 ? exp2f(m - mn) : expf(m - mn), p = l2 ? exp2f(sc - mn) : expf(sc - mn);
+      const float mn = fmaxf(m, sc), mr = mn == -INFINITY ? 0.f : mn;  // (keys that score -inf may come first)
+      const float al = l2 ? exp2f(m - mr) : expf(m - mr), p = l2 ? exp2f(sc - mr) : expf(sc - mr);
       l = l * al + p;
 #pragma unroll
       for (int i = 0; i < DMAX; ++i)

@@ -227,6 +227,34 @@ def test_attention(ops, dt, qmode, heads, d, nq, nk, scale, cross):
         assert err <= tol, (i, err)
 
 
+@pytest.mark.parametrize("log2", [False, True])
+@pytest.mark.parametrize("d,nk,dead", [(8, 8, (3,)), (8, 8, (0,)), (16, 77, tuple(range(10, 77))), (40, 130, (0, 16, 32, 48, 64)),
+                                       (64, 65, tuple(range(64))), (128, 40, (0, 1, 33)), (32, 6, tuple(range(6)))])
+def test_attention_f32_minus_inf_scores(ops, d, nk, dead, log2):
+    """Keys that score -inf have no weight, whichever lane or tile they fall
+    to and also as the first ones; with no other key the result is NaN."""
+    heads, n, nq = 2, 1, 21
+    log(f"attention f32 -inf d={d} nk={nk} dead={len(dead)}")
+    rng = np.random.default_rng(d + nk)
+    C = heads * d
+    q, k, v = (rng.standard_normal((n, t, C)).astype(np.float32) for t in (nq, nk, nk))
+    q[:, :, ::d] = np.abs(q[:, :, ::d]) + 0.1  # channel 0 of each head: positive, so -inf there scores -inf
+    kd = k.copy()
+    kd[:, dead, ::d] = -np.inf
+    o = torch.empty(n, nq, C, device="cuda")
+    ops.attention(_dev(q), _dev(kd), _dev(v), o, n, heads, d, nq, nk, C, nq * C, C, nk * C, C, nk * C, C, nq * C,
+                  1.0 / math.sqrt(d), q_log2=log2)
+    got = o.cpu().numpy()[0].astype(np.float64)
+    if len(dead) == nk:
+        assert np.isnan(got).all()
+        return
+    live = [i for i in range(nk) if i not in dead]
+    qs = q[0].astype(np.float64) * (math.sqrt(d) * math.log(2) if log2 else 1.0)  # base-2 scores, no scale
+    ref = O.attention(qs, k[0][live].astype(np.float64), v[0][live].astype(np.float64), heads)
+    # base-2 scores reach some 20: a relative rounding of 2^-24 each is 1e-6 in the probabilities
+    assert rel_l2(got, ref) <= (1e-5 if log2 else TOL["f32"])
+
+
 @pytest.mark.parametrize("d,nq,nk", [(40, 129, 77), (64, 300, 64), (80, 33, 130), (160, 70, 90), (24, 5, 8)])
 def test_attention_strided_output(ops, d, nq, nk):
     """Output rows wider than the heads (ragged last query block): the columns
