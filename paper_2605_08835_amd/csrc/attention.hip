@@ -545,6 +545,9 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
   static_assert(NW * 32 * LDK <= 2 * KT * LDK, "the waves' rows fit the K tiles");
   bf16* R = &Ks[0][0] + wave * 32 * LDK;
   const int d8 = FAST ? DV / 8 : d >> 3;
+  // 16-byte stores where every row starts at a multiple of 16 bytes, as the
+  // step's do; rows of a caller's wider or offset buffer leave in 8-byte pieces.
+  const bool o16 = (((uint64_t)a.o | (uint64_t)(2 * a.o_ld) | (uint64_t)(2 * a.o_img)) & 15) == 0;
 #pragma unroll
   for (int g = 0; g < QG; ++g) {
     float l = l_run[g];
@@ -571,11 +574,20 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
       }
     asm volatile("" ::: "memory");  // (one wave's LDS accesses complete in order)
     bf16* O = reinterpret_cast<bf16*>(a.o) + (long)img * a.o_img + hd;
-    for (int c = lane; c < 32 * d8; c += 64) {
-      const int row = c / d8, ch = c - row * d8, q = qb + 32 * g + row;
-      if (q < a.Nq)
-        *reinterpret_cast<bf16x8*>(O + (long)q * a.o_ld + 8 * ch) =
-            *reinterpret_cast<const bf16x8*>(R + row * LDK + 8 * ch);
+    if (o16) {
+      for (int c = lane; c < 32 * d8; c += 64) {
+        const int row = c / d8, ch = c - row * d8, q = qb + 32 * g + row;
+        if (q < a.Nq)
+          *reinterpret_cast<bf16x8*>(O + (long)q * a.o_ld + 8 * ch) =
+              *reinterpret_cast<const bf16x8*>(R + row * LDK + 8 * ch);
+      }
+    } else {
+      for (int c = lane; c < 64 * d8; c += 64) {
+        const int row = c / (2 * d8), ch = c - row * (2 * d8), q = qb + 32 * g + row;
+        if (q < a.Nq)
+          *reinterpret_cast<bf16x4*>(O + (long)q * a.o_ld + 4 * ch) =
+              *reinterpret_cast<const bf16x4*>(R + row * LDK + 4 * ch);
+      }
     }
     asm volatile("" ::: "memory");
   }

@@ -255,23 +255,27 @@ def test_attention_f32_minus_inf_scores(ops, d, nk, dead, log2):
     assert rel_l2(got, ref) <= (1e-5 if log2 else TOL["f32"])
 
 
+@pytest.mark.parametrize("pad,off", [(16, 0), (4, 0), (16, 4)])
 @pytest.mark.parametrize("d,nq,nk", [(40, 129, 77), (64, 300, 64), (80, 33, 130), (160, 70, 90), (24, 5, 8)])
-def test_attention_strided_output(ops, d, nq, nk):
+def test_attention_strided_output(ops, d, nq, nk, pad, off):
     """Output rows wider than the heads (ragged last query block): the columns
-    and rows outside the result keep their values."""
+    and rows outside the result keep their values.  Rows may start at multiples
+    of 8 bytes only (pad 4: every other one; off 4: all of them)."""
     heads, n = 2, 2
-    log(f"attention strided output d={d} nq={nq} nk={nk}")
+    log(f"attention strided output d={d} nq={nq} nk={nk} pad={pad} off={off}")
     rng = np.random.default_rng(d + nq)
-    C, pad = heads * d, 16
+    C = heads * d
     q, k, v = (_vals(rng, (n, t, C), "bf16") for t in (nq, nk, nk))
     ld = (nk + 7) // 8 * 8
     vdev = torch.zeros(n, C, ld, device="cuda", dtype=torch.bfloat16)
     vdev[:, :, :nk] = _dev(v, "bf16").transpose(1, 2)
-    o = torch.full((n, nq + 3, C + pad), 7.0, device="cuda", dtype=torch.bfloat16)
+    flat = torch.full((off + n * (nq + 3) * (C + pad),), 7.0, device="cuda", dtype=torch.bfloat16)
+    o = flat[off:]
     ops.attention(_dev(q, "bf16"), _dev(k, "bf16"), vdev, o, n, heads, d, nq, nk, C, nq * C, C, nk * C, ld, C * ld,
                   C + pad, (nq + 3) * (C + pad), 1.0 / math.sqrt(d), v_transposed=True)
     torch.cuda.synchronize()
-    got = o.float().cpu().numpy()
+    assert (flat[:off] == 7.0).all()
+    got = o.float().cpu().numpy().reshape(n, nq + 3, C + pad)
     assert (got[:, nq:] == 7.0).all() and (got[:, :, C:] == 7.0).all()
     for i in range(n):
         ref = O.attention(q[i].astype(np.float64), k[i].astype(np.float64), v[i].astype(np.float64), heads)
