@@ -256,7 +256,8 @@ def test_attention_f32_minus_inf_scores(ops, d, nk, dead, log2):
 
 
 @pytest.mark.parametrize("pad,off", [(16, 0), (4, 0), (16, 4)])
-@pytest.mark.parametrize("d,nq,nk", [(40, 129, 77), (64, 300, 64), (80, 33, 130), (160, 70, 90), (24, 5, 8)])
+@pytest.mark.parametrize("d,nq,nk", [(40, 129, 77), (40, 128, 77), (64, 300, 64), (80, 33, 130), (160, 70, 90),
+                                     (160, 193, 90), (24, 5, 8)])
 def test_attention_strided_output(ops, d, nq, nk, pad, off):
     """Output rows wider than the heads (ragged last query block): the columns
     and rows outside the result keep their values.  Rows may start at multiples
