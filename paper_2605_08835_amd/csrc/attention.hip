@@ -621,14 +621,18 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
   }
 }
 
-// fp32, heads up to 64 wide: 16 lanes per query, each over the keys of its
+// fp32, heads up to 64 wide: LQ = 16 lanes per query, each over the keys of its
 // residue mod 16 with its own online softmax (four keys of a 64-key LDS tile
 // at a time), merged at the end, so that a query's chain is Nk / 64 tiles of
 // four keys instead of Nk keys: 256 queries x 256 keys, 4 heads of 8, 3 images
-// 272 -> 15 us.  (A thread per query left 48 waves on the chip.)
-template <int DMAX>
+// 272 -> 15 us.  (A thread per query left 48 waves on the chip.)  Up to 32 keys
+// take LQ = 4 and tiles of 16: with 16 lanes most of the keys that a lane
+// multiplies and merges would not exist (64 images of 900 queries, 4 heads of 8,
+// 8 keys: 16 us against 40, a thread per query 22).  The form follows the key
+// count, never the rows.
+template <int DMAX, int LQ>
 __global__ __launch_bounds__(256) void attn_f32_lanes_kernel(AttnArgs a) {
-  constexpr int KTF = 64, LQ = 16, QB = 256 / LQ, KL = KTF / LQ, LD = DMAX + 4;
+  constexpr int KL = 4, KTF = KL * LQ, QB = 256 / LQ, LD = DMAX + 4;
   __shared__ __attribute__((aligned(16))) float Ks[KTF * LD];
   __shared__ __attribute__((aligned(16))) float Vs[KTF * LD];
   const int tid = threadIdx.x, part = tid & (LQ - 1);
@@ -702,7 +706,7 @@ __global__ __launch_bounds__(256) void attn_f32_lanes_kernel(AttnArgs a) {
       m = mn;
     }
   }
-  // merge the 16 lanes of the query (a lane that saw no key has m = -inf, l = 0)
+  // merge the lanes of the query (a lane that saw no key has m = -inf, l = 0)
 #pragma unroll
   for (int off = LQ / 2; off > 0; off >>= 1) {
     const float m2 = __shfl_xor(m, off, 64), l2s = __shfl_xor(l, off, 64);
@@ -726,7 +730,15 @@ __global__ __launch_bounds__(256) void attn_f32_lanes_kernel(AttnArgs a) {
   }
 }
 
-// fp32, wider heads: one thread per query.
+// fp32, wider heads, and a single key (nothing to share out): one thread per query.
+template <int DMAX>
+static void launch_f32_lanes(const AttnArgs& a, hipStream_t s) {
+  if (a.Nk <= 32)
+    attn_f32_lanes_kernel<DMAX, 4><<<dim3((a.Nq + 63) / 64, a.heads, a.imgs), 256, 0, s>>>(a);
+  else
+    attn_f32_lanes_kernel<DMAX, 16><<<dim3((a.Nq + 15) / 16, a.heads, a.imgs), 256, 0, s>>>(a);
+}
+
 template <int DMAX, int KTF>
 __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
   __shared__ float Ks[KTF * DMAX];
@@ -835,17 +847,21 @@ hipError_t launch_attention(DType dt, const AttnArgs& a, hipStream_t s) {
     }
   } else {
     if (a.vt || a.d <= 0) return hipErrorInvalidValue;
-    dim3 grid((a.Nq + 63) / 64, a.heads, a.imgs), lgrid((a.Nq + 15) / 16, a.heads, a.imgs);
+    dim3 grid((a.Nq + 63) / 64, a.heads, a.imgs);
     // (the wide heads keep q and o in scratch: the fp32 path is the
     // reference-precision path for small configurations, not a fast one)
-    if (a.d <= 8)
-      attn_f32_lanes_kernel<8><<<lgrid, 256, 0, s>>>(a);
+    if (a.Nk == 1 && a.d <= 16)
+      attn_f32_kernel<16, 64><<<grid, 64, 0, s>>>(a);
+    else if (a.Nk == 1 && a.d <= 64)
+      attn_f32_kernel<64, 64><<<grid, 64, 0, s>>>(a);
+    else if (a.d <= 8)
+      launch_f32_lanes<8>(a, s);
     else if (a.d <= 16)
-      attn_f32_lanes_kernel<16><<<lgrid, 256, 0, s>>>(a);
+      launch_f32_lanes<16>(a, s);
     else if (a.d <= 32)
-      attn_f32_lanes_kernel<32><<<lgrid, 256, 0, s>>>(a);
+      launch_f32_lanes<32>(a, s);
     else if (a.d <= 64)
-      attn_f32_lanes_kernel<64><<<lgrid, 256, 0, s>>>(a);
+      launch_f32_lanes<64>(a, s);
     else if (a.d <= 128)
       attn_f32_kernel<128, 32><<<grid, 64, 0, s>>>(a);
     else if (a.d <= 256)

@@ -255,6 +255,30 @@ def test_attention_f32_minus_inf_scores(ops, d, nk, dead, log2):
     assert rel_l2(got, ref) <= (1e-5 if log2 else TOL["f32"])
 
 
+@pytest.mark.parametrize("d", [8, 16, 40, 64])
+@pytest.mark.parametrize("nk", [1, 2, 16, 17, 32, 33, 65])
+def test_attention_f32_key_counts(ops, d, nk):
+    """fp32 attention at the edges of its forms (1, up to 32 and more keys),
+    ragged query blocks; the first image alone gives the same bits."""
+    heads, n, nq = 3, 2, 70
+    log(f"attention f32 keys d={d} nk={nk}")
+    rng = np.random.default_rng(100 * d + nk)
+    C = heads * d
+    q, k, v = (rng.standard_normal((n, t, C)).astype(np.float32) for t in (nq, nk, nk))
+
+    def run(m):
+        o = torch.empty(m, nq, C, device="cuda")
+        ops.attention(_dev(q), _dev(k), _dev(v), o, m, heads, d, nq, nk, C, nq * C, C, nk * C, C, nk * C, C, nq * C,
+                      1.0 / math.sqrt(d))
+        return o.cpu().numpy()
+
+    got = run(n)
+    assert np.array_equal(run(1), got[:1])
+    for i in range(n):
+        ref = O.attention(*(t[i].astype(np.float64) for t in (q, k, v)), heads)
+        assert rel_l2(got[i], ref) <= TOL["f32"]
+
+
 @pytest.mark.parametrize("pad,off", [(16, 0), (4, 0), (16, 4)])
 @pytest.mark.parametrize("d,nq,nk", [(40, 129, 77), (40, 128, 77), (64, 300, 64), (80, 33, 130), (160, 70, 90),
                                      (160, 193, 90), (24, 5, 8)])
