@@ -217,15 +217,32 @@ __global__ __launch_bounds__(256) void linear_smallm_kernel(const float* in, int
   }
 }
 
+// Adds up H entries per lane over the wave by halving: a step keeps the half of
+// a lane's entries that the lane bit OFF selects and adds the partner's copy of
+// it, until one entry is left.
+template <int H, int OFF, int E>
+__device__ __forceinline__ void halve_entries(float (&acc)[E], int lane) {
+  if constexpr (H > 1) {
+    const bool hi = (lane & OFF) != 0;
+#pragma unroll
+    for (int i = 0; i < H / 2; ++i) {
+      const float keep = hi ? acc[i + H / 2] : acc[i], give = hi ? acc[i] : acc[i + H / 2];
+      acc[i] = keep + __shfl_xor(give, OFF, 64);
+    }
+    halve_entries<H / 2, OFF / 2>(acc, lane);
+  }
+}
+
 // The same for at most MB rows (2, 4 or 8; a request or a few): the 32-row
 // form multiplies and exchanges its empty rows too, and loads a chunk of
 // weights between two barriers.  Here all of x is staged once and the weight
 // loads of four chunks are in flight.  The order of the sums is that of the
 // 32-row form (each lane's chunks in order, then lanes 32, 16, .. 1 apart), so
 // a row's bits do not depend on which form runs.  The three launches of a
-// step for one guided request of the SD-1.5 UNet: 101 -> 44 us.
+// step for one guided request of the SD-1.5 UNet: 101 -> 44 us.  Five blocks per
+// CU (96 registers) up to 4 rows: 2 rows of 1280 x 20160 20.0 us with four.
 template <typename TW, int MB>
-__global__ __launch_bounds__(256) void linear_fewm_kernel(const float* in, int M, int K, const TW* W,
+__global__ __launch_bounds__(256, MB == 8 ? 4 : 5) void linear_fewm_kernel(const float* in, int M, int K, const TW* W,
                                                           const float* bias, const float* add, float* out, int N,
                                                           int silu_in, int silu_out) {
   using namespace sm;
@@ -246,11 +263,10 @@ __global__ __launch_bounds__(256) void linear_fewm_kernel(const float* in, int M
     *reinterpret_cast<float4*>(&xf[m * KR + kk]) = v;
   }
   __syncthreads();
-  float acc[CPW][MB];
+  constexpr int E = CPW * MB;  // entries (column, row) = c * MB + m
+  float acc[E];
 #pragma unroll
-  for (int c = 0; c < CPW; ++c)
-#pragma unroll
-    for (int m = 0; m < MB; ++m) acc[c][m] = 0.f;
+  for (int i = 0; i < E; ++i) acc[i] = 0.f;
   for (int k0 = 0; k0 < K; k0 += U * KC) {
     float w[U][CPW][4];
 #pragma unroll
@@ -272,31 +288,30 @@ __global__ __launch_bounds__(256) void linear_fewm_kernel(const float* in, int M
           const float4 x = *reinterpret_cast<const float4*>(&xf[m * KR + k]);
 #pragma unroll
           for (int c = 0; c < CPW; ++c) {
-            float t = acc[c][m];
+            float t = acc[c * MB + m];
             t = fmaf(x.x, w[u][c][0], t);
             t = fmaf(x.y, w[u][c][1], t);
             t = fmaf(x.z, w[u][c][2], t);
             t = fmaf(x.w, w[u][c][3], t);
-            acc[c][m] = t;
+            acc[c * MB + m] = t;
           }
         }
       }
     }
   }
+  // (a full exchange of each of the E entries took 6 E steps: 8 rows of 32 x 128
+  // 12.7 us, now 4.4, the 32-row form 8.8)
+  halve_entries<E, 32>(acc, lane);
+  constexpr int LPE = 64 / E;  // lanes that hold the same entry, lane / LPE
+  float v = acc[0];
 #pragma unroll
-  for (int c = 0; c < CPW; ++c)
-#pragma unroll
-    for (int m = 0; m < MB; ++m) {
-      float v = acc[c][m];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      const int n = n0 + c;
-      if (lane == c * MB + m && n < N && m < M) {
-        v = v + (bias ? bias[n] : 0.f) + (add ? add[(long)m * N + n] : 0.f);
-        if (silu_out) v = silu_f(v);
-        out[(long)m * N + n] = v;
-      }
-    }
+  for (int o = LPE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  const int n = n0 + lane / (LPE * MB), m = lane / LPE % MB;
+  if (lane % LPE == 0 && n < N && m < M) {
+    v = v + (bias ? bias[n] : 0.f) + (add ? add[(long)m * N + n] : 0.f);
+    if (silu_out) v = silu_f(v);
+    out[(long)m * N + n] = v;
+  }
 }
 
 template <typename TW>
