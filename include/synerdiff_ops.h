@@ -95,9 +95,10 @@ sd_status synerdiff_op_groupnorm_stats(int32_t dtype, const void* d_x0, int32_t 
  * allocates nothing.  A call whose partial sums exceed that size, counting
  * at most 64 pixel ranges per image (2 (c0 + c1) floats each), returns
  * SD_ERR_CAPACITY before enqueueing anything; one whose partials only exceed
- * it at the finer ranges of large images runs in several passes.  Every call on a device
- * shares its array: calls that overlap in time on one device (different
- * streams or host threads) race.  Each call writes every partial it reads,
+ * it at the finer ranges of larger images runs in several passes, one after
+ * the other on the stream.  Every call on a device shares its array: calls
+ * that overlap in time on one device (different streams or host threads)
+ * race.  Each call writes every partial it reads,
  * so no clearing is needed between calls.  Arguments and outputs as for
  * synerdiff_op_groupnorm_stats. */
 #define SYNERDIFF_GN_NOALLOC_SCRATCH_FLOATS (1u << 22)

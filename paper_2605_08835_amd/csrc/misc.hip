@@ -355,14 +355,18 @@ static inline int gn_pp(int cin) {
   const int cv = cin / 8;
   return cv >= 512 ? 1 : 512 / cv;
 }
-// Splits of an image's pixels (about 16 pixels per thread, at most 256):
-// 16 measured 7 % faster than 8 per launch at the SD-1.5 widths (fewer
-// blocks, the LDS reduction amortised over more loads).  A single 512x512
-// image of the VAE decoder needs the 256 (one block per CU): with 64 its
-// 256-channel pass took 122 us, the 30 passes of a decode 0.73 ms; now the
-// decode is 0.3 ms (7 %) faster.
-static inline int gn_splits(int hw, int cin, int most = 256) {
-  const int s = hw / (gn_pp(cin) * 16);
+
+// Splits of an image's pixels (about 16 pixels per thread): 16 measured 7 %
+// faster than 8 per launch at the SD-1.5 widths (fewer blocks, the LDS
+// reduction amortised over more loads).  At most 128: a batch fills the chip with
+// 64, and more blocks only cost it their start and reduction (16 images of
+// 128x128x960 101 us with 64 or 128, 111 with 256), but one or two images do not
+// (2 of them 30, 20 and 19 us).  From 2^15 pixels on, the VAE decoder's large
+// images, which come one or two at a time, at most 256, one block per CU
+// (512x512x256 81 us with 64, 28 with 256; eight of 256x256x512 97 and 102).
+// A function of the image alone, so its bits do not depend on the batch.
+static inline int gn_splits(int hw, int cin, bool few = false) {
+  const int s = hw / (gn_pp(cin) * 16), most = few ? 64 : (hw >= (1 << 15) ? 256 : 128);
   return s < 1 ? 1 : (s > most ? most : s);
 }
 
@@ -374,18 +378,20 @@ size_t groupnorm_partial_floats(int imgs, int hw, int cin) {
 // (64 splits an image at most); a call whose partials exceed the scratch at
 // the full split count runs its images in several passes.
 size_t groupnorm_noalloc_floats(int imgs, int hw, int cin) {
-  return (size_t)imgs * gn_splits(hw, cin, 64) * cin * 2;
+  return (size_t)imgs * gn_splits(hw, cin, true) * cin * 2;
 }
 
 // Pass 1: per (image, split, channel) sum and sum of squares (fp32 over at
 // most a few hundred pixels; the finalize pass adds the splits in fp64).
 // Thread (pp, cv) reads channels 8 cv .. 8 cv + 7 (one 16-byte load) of
 // pixels pp, pp + PP, ..., four at a time so their loads overlap; the
-// partial results are reduced over pp in LDS.
+// partial results are reduced over pp in LDS, laid out so that neighbouring
+// lanes write and read neighbouring 16-byte pieces (written channel by channel,
+// 16 lanes met in each bank: 48 images of 64x64x640 52.4 us, now 44.7).
 template <typename T>
 __global__ void gn_partial_kernel(const T* src0, int c0, const T* src1, int c1, int hw, int nsplit,
                                   int PP, float* partial) {
-  extern __shared__ float red[];  // [PP][cin][2]
+  extern __shared__ __attribute__((aligned(16))) float4 red[];  // [PP][4 channel pairs][CV]: sum, squares of each
   const int cin = c0 + c1, CV = cin / 8;
   const int img = blockIdx.y, split = blockIdx.x;
   const int chunk = (hw + nsplit - 1) / nsplit;
@@ -417,26 +423,25 @@ __global__ void gn_partial_kernel(const T* src0, int c0, const T* src1, int c1, 
         }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      red[((long)pp * cin + c + i) * 2] = s[i];
-      red[((long)pp * cin + c + i) * 2 + 1] = q[i];
-    }
+    for (int j = 0; j < 4; ++j)
+      red[(pp * 4 + j) * CV + cv] = make_float4(s[2 * j], q[2 * j], s[2 * j + 1], q[2 * j + 1]);
   }
   __syncthreads();
-  for (int ch = threadIdx.x; ch < cin; ch += blockDim.x) {
-    float ss = 0.f, qq = 0.f;
+  for (int i = threadIdx.x; i < 4 * CV; i += blockDim.x) {
+    const int j = i / CV, v = i - j * CV;
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int k = 0; k < PP; ++k) {
-      ss += red[((long)k * cin + ch) * 2];
-      qq += red[((long)k * cin + ch) * 2 + 1];
+      const float4 r = red[k * 4 * CV + i];
+      t.x += r.x; t.y += r.y; t.z += r.z; t.w += r.w;
     }
-    float* o = partial + (((long)img * nsplit + split) * cin + ch) * 2;
-    o[0] = ss;
-    o[1] = qq;
+    float2* o = reinterpret_cast<float2*>(partial + (((long)img * nsplit + split) * cin + 8 * v + 2 * j) * 2);
+    o[0] = make_float2(t.x, t.y);
+    o[1] = make_float2(t.z, t.w);
   }
 }
 
 // Pass 2: per (image, group) mean and rstd in fp64 -> the per-channel affine.
-// One block per (group, image), a wave where a lane then adds at most 16
+// One block per (group, image), a wave where a lane then adds at most 10
 // partials, else four; the loads of a lane's partials are independent, so the
 // loop is unrolled to keep them in flight together.
 template <int NW>
@@ -501,7 +506,7 @@ hipError_t launch_groupnorm_stats(DType dt, const void* src0, int c0, const void
                                                         c1, hw, nsplit, PP, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (nsplit * (cin / groups) <= 16 * 64)
+  if (nsplit * (cin / groups) <= 10 * 64)
     gn_finalize_kernel<1><<<dim3(groups, imgs), 64, 0, s>>>(partial, cin, nsplit, hw, groups, eps, gamma, beta,
                                                             scale, shift);
   else
