@@ -101,6 +101,10 @@ CONFIGS = {
                       cfg=("fixed", (1, 0, 1)), guidance=("uniform", 5.0, 9.0)),
     "t_tiny_f32_v": dict(unet=_with(TINY, prediction="v", schedule="scaled_linear"), requests=2,
                          t=("uniform",), cfg=("fixed", (1, 0)), guidance=("uniform", 5.0, 9.0)),
+    # Larger fp32 images: the one-kernel GroupNorm beyond 1024 vectors a group,
+    # groups that straddle the two sources of a concat.
+    "t_tiny_f32_30": dict(unet=_with(TINY, latent_h=30, latent_w=34), requests=2, t=("uniform",), cfg=("fixed", (1, 0)),
+                          guidance=("uniform", 5.0, 9.0)),
     "t_tiny_f32_ragged": dict(unet=_with(TINY, latent_h=12, latent_w=20),
                               requests=3, t=("uniform",), cfg=("fixed", (0, 1, 1)),
                               guidance=("uniform", 5.0, 9.0)),

@@ -67,6 +67,13 @@ def test_tiny_f32_ragged_step(weights_cache):
     check("t_tiny_f32_ragged", weights_cache)
 
 
+def test_tiny_f32_30px_step(weights_cache):
+    """The fp32 one-kernel GroupNorm's larger form: 1020 and 2040 to 3060
+    vectors a group at 30x34 (32, 64 and 64 + 32 channels in 8 groups), the
+    last with groups across the two sources."""
+    check("t_tiny_f32_30", weights_cache)
+
+
 def test_tiny_bf16_step(weights_cache):
     check("t_tiny_bf16", weights_cache)
 

@@ -43,6 +43,27 @@ def test_noalloc_matches_the_allocating_entry_point_twice(dt):
         assert torch.equal(sc, ref_sc) and torch.equal(sh, ref_sh)
 
 
+@pytest.mark.parametrize("n,H,W,c0,c1", [(5, 64, 64, 4096, 0), (5, 64, 64, 2048, 2048), (9, 181, 183, 1024, 64)])
+def test_noalloc_in_several_passes(n, H, W, c0, c1):
+    """Calls whose partial sums exceed the scratch at their full range count:
+    several passes, the last one with fewer images, give the bits of the entry
+    point that takes a buffer, for every image and both sources."""
+    from paper_2605_08835_amd import lib, ops
+    cin, most = c0 + c1, 1 << 22
+    one = lib().synerdiff_op_groupnorm_scratch_floats(1, H * W, cin)
+    per = most // one
+    assert n * one > most and 1 < per < n and n % per  # several passes, a ragged last one
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(c0)
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
+    x0, x1 = r(n, H, W, c0).to(torch.bfloat16), r(n, H, W, c1).to(torch.bfloat16) if c1 else None
+    g, b = 1 + 0.1 * r(cin), 0.1 * r(cin)
+    ref_sc, ref_sh = ops.groupnorm_stats(x0, 32, 1e-5, g, b, x1=x1)
+    sc, sh = ops.groupnorm_stats_noalloc(x0, 32, 1e-5, g, b, x1=x1)
+    torch.cuda.synchronize()
+    assert torch.equal(sc, ref_sc) and torch.equal(sh, ref_sh)
+
+
 def test_noalloc_rejects_more_than_its_scratch():
     from paper_2605_08835_amd import lib, ops
     from paper_2605_08835_amd.binding import SynerDiffError
