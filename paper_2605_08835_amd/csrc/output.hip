@@ -30,10 +30,13 @@
 
 namespace sd {
 
-// WIDE: 8 waves, four on each of a request's two rows at the same time (all
-// eight on the only row under Skip-CFG), each row with its own Y; threads
-// 0..255 gather the conditional, 256..511 the unconditional eps.  Else 4 waves,
-// one row after the other, two blocks per CU.  a.P output pixels per block.
+// WIDE: 8 waves, four on each of a request's two rows at the same time, each
+// row with its own Y; threads 0..255 gather the conditional, 256..511 the
+// unconditional eps.  Under Skip-CFG all eight take the only row where a block
+// has 64 pixels, else four (the others' weight loads cost more than their tiles
+// save: 10 requests of 64x64 15.3 us with eight, 14.6 with four).
+// Not WIDE: 4 waves, one row after the other, two blocks per CU.  a.P output
+// pixels per block.
 template <int S, bool WIDE>  // S = C / 32 MFMA steps over the channels
 __global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 1 : 2) void out_cfg_ddim_kernel(OutArgs a) {
   extern __shared__ __attribute__((aligned(16))) float Ys[];  // (two of) [pixel - q0][9 taps][4], eps_u
@@ -55,6 +58,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 1 : 2) void out_cfg_ddim_k
     bias[c] = a.bias[c];
     lat[c] = p < p1 ? a.lat_in[((long)r * 4 + c) * HW + p] : 0.f;
   }
+  const int nw1 = WIDE && a.P < 128 ? 8 : 4;  // waves on the only row of a request
+  const bool idle = WIDE && ru < 0 && wave >= nw1;
   // weight fragments: tile t, row pl is column j = 16 t + pl = (tap j / 4, output j % 4)
   bf16x8 wf[3][S];
 #pragma unroll
@@ -63,7 +68,7 @@ __global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 1 : 2) void out_cfg_ddim_k
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       bf16x8 v = {};
-      if (j < 36) v = *reinterpret_cast<const bf16x8*>(a.w + (long)o * 9 * C + tap * C + 32 * s + 8 * g);
+      if (j < 36 && !idle) v = *reinterpret_cast<const bf16x8*>(a.w + (long)o * 9 * C + tap * C + 32 * s + 8 * g);
       wf[t][s] = v;
     }
   }
@@ -130,8 +135,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 1 : 2) void out_cfg_ddim_k
     float* E = Ys + 2 * ylen;  // eps_u of the block's pixels
     if (ru >= 0)
       compute_y(half ? ru : r, Ys + half * ylen, wave & 3, 4);
-    else
-      compute_y(r, Ys, wave, 8);
+    else if (!idle)
+      compute_y(r, Ys, wave, nw1);
     __syncthreads();
     if (half == 0) {
       gather(Ys, ec);
@@ -187,17 +192,20 @@ static hipError_t launch_out_k(const OutArgs& a, unsigned blocks, hipStream_t s)
   return hipGetLastError();
 }
 
-// Blocks of 256 pixels, two per CU, once they fill most of the chip; fewer
-// take the 8-wave form (one block per CU), with 128 or 64 pixels where that
-// still leaves at most a block per CU (the halo of 2 W + 2 pixels is
+// Blocks of 256 pixels, two per CU, once there are more of them than CUs; up to
+// that many take the 8-wave form (one block per CU), with 128 or 64 pixels
+// where that still leaves at most a block per CU (the halo of 2 W + 2 pixels is
 // recomputed per block).  The pixels per block do not enter the arithmetic.
 // 64x64x320, guided: one request 22.3 us with 256 pixels, 15.9 with 64; eight
-// 23.0 with 256, 20.0 with 128; twelve 23.1 in either form.
+// 23.0 with 256, 20.0 with 128; sixteen (256 blocks) 26.2 with 4 waves, 25.4
+// with 8; past 256 blocks the 8-wave form needs a second round: 20 requests
+// 45.1 us with 8 waves, 36.0 with 4; without guidance 29.2 and 22.4; at 64
+// channels 13.6 and 10.9.
 template <int S>
 static hipError_t launch_out_s(OutArgs a, hipStream_t s) {
   const int HW = a.H * a.W;
   auto blocks = [&](int P) { return (long)a.n_req * ((HW + P - 1) / P); };
-  const bool wide = blocks(256) < 384;
+  const bool wide = blocks(256) <= 256;
   a.P = !wide ? 256 : (blocks(64) <= 256 ? 64 : (blocks(128) <= 256 ? 128 : 256));
   a.tiles = (HW + a.P - 1) / a.P;
   if (blocks(a.P) > 0x7FFFFFFFL) return hipErrorInvalidValue;
