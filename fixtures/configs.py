@@ -105,6 +105,9 @@ CONFIGS = {
     # groups that straddle the two sources of a concat.
     "t_tiny_f32_30": dict(unet=_with(TINY, latent_h=30, latent_w=34), requests=2, t=("uniform",), cfg=("fixed", (1, 0)),
                           guidance=("uniform", 5.0, 9.0)),
+    # 23040 pixel rows: the fp32 GEMM's 64x64 tiles, two-segment layers among them.
+    "t_tiny_f32_72": dict(unet=_with(TINY, latent_h=64, latent_w=72), requests=3, t=("uniform",),
+                          cfg=("fixed", (1, 0, 1)), guidance=("uniform", 5.0, 9.0)),
     "t_tiny_f32_ragged": dict(unet=_with(TINY, latent_h=12, latent_w=20),
                               requests=3, t=("uniform",), cfg=("fixed", (0, 1, 1)),
                               guidance=("uniform", 5.0, 9.0)),

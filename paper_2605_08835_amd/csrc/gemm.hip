@@ -1111,18 +1111,24 @@ __global__ void splitk_reduce_kernel(GemmArgs a) {
 // depend on the tile or on its batch-mates.  Against 64x64 SIMT tiles with a
 // barrier every 16 k (event to event, some 5 us of it the launch): 192 x 64 x
 // 576 50 -> 8.9 us, 192 x 64 x 1152 93 -> 11.4 us, 768 x 32 x 32 10.5 -> 6.5 us.
+// (tap, channel) of k: k / cin by a float quotient corrected by one (exact below 2^24)
+__device__ __forceinline__ void split_k(int k, int cin, float inv_cin, int& tap, int& c) {
+  tap = (int)((float)k * inv_cin);
+  c = k - tap * cin;
+  if (c < 0) {
+    --tap;
+    c += cin;
+  } else if (c >= cin) {
+    ++tap;
+    c -= cin;
+  }
+}
+
 template <typename T4>
 __device__ __forceinline__ void a_quad(const ASeg& s, const RowPos& r, int k, float inv_cin, T4& v) {
   v = T4{0.f, 0.f, 0.f, 0.f};
-  // k / cin by a float quotient corrected by one (exact below 2^24)
-  int tap = (int)((float)k * inv_cin), c = k - tap * s.cin;
-  if (c < 0) {
-    --tap;
-    c += s.cin;
-  } else if (c >= s.cin) {
-    ++tap;
-    c -= s.cin;
-  }
+  int tap, c;
+  split_k(k, s.cin, inv_cin, tap, c);
   const float* p = a_chunk_ptr<float>(s, r, tap, c);
   if (!p) return;
   v = *reinterpret_cast<const T4*>(p);
@@ -1220,13 +1226,198 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmArgs a) {
   }
 }
 
+// The same sums for large layers, where the form above is bound by its operand
+// traffic (a 32x32 tile reads 256 bytes per k for 1024 products): a block of 4
+// waves is one 64x64 tile whose 16-deep chunks go through LDS, two to a stage,
+// the next stage's loads in flight beside the products.  Chunk c adds to partial
+// sum c mod NW of each output, and the NW partial sums are added in order at the
+// end, so an output has the bits of the form above.  A thread fetches one quad
+// of A and one of B per chunk; a chunk lies in LDS as [row][16 k], so both the
+// quads' writes and the fragment reads are contiguous.  What bounds it is issue:
+// 16 products (512 cycles) a chunk beside the addressing of two quads, two waves
+// per SIMD; 62 TFLOP/s at 32768 x 1280 x 320, 73 at 4096 x 512 x 4608.
+template <int NW>
+__global__ __launch_bounds__(256, 2) void gemm_f32_tiled_kernel(GemmArgs a) {
+  constexpr int BT = 64, CH = 2;  // tile edge; chunks per stage
+  __shared__ __attribute__((aligned(16))) float As[2][CH][BT * 16], Bs[2][CH][BT * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int tiles_n = (a.N + BT - 1) / BT;
+  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
+  const int m0 = tm * BT, n0 = tn * BT;
+  const int kq = 4 * (tid & 3);  // of the quad this thread fetches, in row tid / 4
+  const RowPos rp = decode_row(a.seg[0], m0 + (tid >> 2), a.M);
+  const bool bok = n0 + (tid >> 2) < a.N;
+  const float* bp = reinterpret_cast<const float*>(a.B) + (bok ? (long)(n0 + (tid >> 2)) * a.ldb : 0);
+  const int K0 = a.seg[0].K;
+  const float inv0 = 1.0f / (float)a.seg[0].cin, inv1 = a.seg[1].K ? 1.0f / (float)a.seg[1].cin : 0.f;
+  const int nst = (a.K + 16 * CH - 1) / (16 * CH);
+
+  // The loads have no branches: a masked quad reads the start of its buffer
+  // and becomes zero, and the GroupNorm affine is applied, when the stage goes
+  // to LDS behind the products.
+  const float* ap[CH];
+  int ac[CH];  // channel, or -1 where the quad is zero
+  auto locate = [&](const ASeg& s, int k, float inv, int c) __attribute__((always_inline)) {
+    int tap, ch;
+    split_k(k, s.cin, inv, tap, ch);
+    int ky = 1, kx = 1;
+    if (s.ks == 3) {
+      ky = tap / 3;
+      kx = tap - ky * 3;
+    }
+    int iy = rp.oy * s.stride + ky - 1, ix = rp.ox * s.stride + kx - 1;
+    const bool ok = rp.ok && iy >= 0 && ix >= 0 && iy < (s.up ? 2 * s.Hi : s.Hi) && ix < (s.up ? 2 * s.Wi : s.Wi);
+    iy >>= s.up ? 1 : 0;
+    ix >>= s.up ? 1 : 0;
+    const bool in0 = ch < s.c0;
+    const float* src = reinterpret_cast<const float*>(in0 ? s.src0 : s.src1);
+    const long off = (((long)rp.img * s.Hi + iy) * s.Wi + ix) * (in0 ? s.c0 : s.c1) + (in0 ? ch : ch - s.c0);
+    ap[c] = src + (ok ? off : 0);
+    ac[c] = ok ? ch : -1;
+  };
+  f32x4 av[CH], bv[CH], asc[CH], ash[CH];
+  auto gload = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int k = 16 * (st * CH + c) + kq, kk = min(k, a.K - 4);
+      if (kk < K0)
+        locate(a.seg[0], kk, inv0, c);
+      else
+        locate(a.seg[1], kk - K0, inv1, c);
+      if (k >= a.K) ac[c] = -1;
+      av[c] = *reinterpret_cast<const f32x4*>(ap[c]);
+      bv[c] = *reinterpret_cast<const f32x4*>(bp + kk);
+      if (a.seg[0].scale) {  // (only ever on a layer of one segment)
+        const long o = (long)rp.img * a.seg[0].cin + max(ac[c], 0);
+        asc[c] = *reinterpret_cast<const f32x4*>(a.seg[0].scale + o);
+        ash[c] = *reinterpret_cast<const f32x4*>(a.seg[0].shift + o);
+      }
+    }
+  };
+  auto sstore = [&](int st, int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      f32x4 v = av[c], w = bv[c];
+      if (a.seg[0].scale) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          v[i] = v[i] * asc[c][i] + ash[c][i];
+          if (a.seg[0].silu) v[i] = silu_f(v[i]);
+        }
+      }
+      const bool kin = 16 * (st * CH + c) + kq < a.K && bok;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = ac[c] >= 0 ? v[i] : 0.f;
+        w[i] = kin ? w[i] : 0.f;
+      }
+      *reinterpret_cast<f32x4*>(&As[buf][c][4 * tid]) = v;
+      *reinterpret_cast<f32x4*>(&Bs[buf][c][4 * tid]) = w;
+    }
+  };
+  f32x4 acc[NW][2][2];
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[w][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  gload(0);
+  sstore(0, 0);
+  __syncthreads();
+  for (int s0 = 0; s0 < nst; s0 += NW / CH) {
+    static_for<0, NW / CH>([&](auto S) {
+      const int st = s0 + S.value, buf = st & 1;
+      if (st < nst) {  // (uniform)
+        if (st + 1 < nst) gload(st + 1);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+          // fragment: lane l holds row l % 16, k 4 (l / 16) .. + 3
+          f32x4 fa[2], fb[2];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            fa[t] = *reinterpret_cast<const f32x4*>(&As[buf][c][(32 * wm + 16 * t + (lane & 15)) * 16 + 4 * (lane >> 4)]);
+            fb[t] = *reinterpret_cast<const f32x4*>(&Bs[buf][c][(32 * wn + 16 * t + (lane & 15)) * 16 + 4 * (lane >> 4)]);
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j)
+                acc[S.value * CH + c][i][j] =
+                    __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[S.value * CH + c][i][j], 0, 0, 0);
+        }
+        if (st + 1 < nst) sstore(st + 1, buf ^ 1);
+        __syncthreads();
+      }
+    });
+  }
+  // (weights as the first operand: lane l holds row l % 16, columns 4 (l / 16) +
+  // [0, 4) of each 16x16 tile)
+  const Epi& e = a.epi;
+  const float* resid = reinterpret_cast<const float*>(e.resid);
+  float* out = reinterpret_cast<float*>(e.out);
+  const bool vec = !((a.N | e.ldo | (resid ? e.ldr : 0) | (e.tbias ? e.tb_ld | e.tb_off : 0)) & 3) &&
+                   !(((uint64_t)out | (uint64_t)resid | (uint64_t)e.bias | (uint64_t)e.tbias) & 15);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = m0 + 32 * wm + 16 * i + (lane & 15);
+    if (row >= a.M) continue;
+    const float* tb = e.tbias ? e.tbias + (long)(row / e.hw) * e.tb_ld + e.tb_off : nullptr;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + 32 * wn + 16 * j + 4 * (lane >> 4);
+      f32x4 v = acc[0][i][j];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += acc[w][i][j];
+      f32x4 b{}, t{}, r{};
+      if (vec && col < a.N) {
+        if (e.bias) b = *reinterpret_cast<const f32x4*>(e.bias + col);
+        if (tb) t = *reinterpret_cast<const f32x4*>(tb + col);
+        if (resid) r = *reinterpret_cast<const f32x4*>(resid + (long)row * e.ldr + col);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (col + q < a.N) {
+            if (e.bias) b[q] = e.bias[col + q];
+            if (tb) t[q] = tb[col + q];
+            if (resid) r[q] = resid[(long)row * e.ldr + col + q];
+          }
+      }
+      v = v + b + t + r;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (col + q < e.qcols) v[q] *= e.qscale;
+      float* o = out + (long)row * e.ldo + col;
+      if (vec) {
+        if (col < a.N) *reinterpret_cast<f32x4*>(o) = v;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (col + q < a.N) o[q] = v[q];
+      }
+    }
+  }
+}
+
 // K split over 8 waves from K = 256 on, else 4 or 2 (a function of K alone);
 // 32x32 tiles (half the operand traffic) once 16x16 ones would give the chip
-// over four blocks per CU.
+// over four blocks per CU; 64x64 tiles through LDS once they give every CU one,
+// unless at most 16 columns use them.  Small form against the LDS one, us: 160
+// blocks of 64x64 (512 x 1280 x 1280) 51 and 57, 192 (12288 x 32 x 288) 13.7 and
+// 16.8; 256 (16384 x 64 x 576) 36.5 and 27.0, 320 (2048 x 640 x 5760) 346 and
+// 323, 640 (8192 x 320 x 320) 65 and 38, 10240 (32768 x 1280 x 320) 1007 and 431;
+// 65536 x 8 x 1152 120 and 134.
 template <int NW>
 static void launch_f32(const GemmArgs& a, hipStream_t s) {
   auto blocks = [&](long bt) { return ((a.M + bt - 1) / bt) * ((a.N + bt - 1) / bt); };
-  if (blocks(16) > 1024)
+  const bool affine2 = a.seg[1].K && (a.seg[0].scale || a.seg[1].scale);  // (the tiled form's affine is for one segment)
+  if (blocks(64) >= 256 && a.N > 16 && !affine2)
+    gemm_f32_tiled_kernel<NW><<<dim3((unsigned)blocks(64)), dim3(256), 0, s>>>(a);
+  else if (blocks(16) > 1024)
     gemm_f32_kernel<2, NW><<<dim3((unsigned)blocks(32)), dim3(64 * NW), 0, s>>>(a);
   else
     gemm_f32_kernel<1, NW><<<dim3((unsigned)blocks(16)), dim3(64 * NW), 0, s>>>(a);

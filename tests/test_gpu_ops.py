@@ -549,9 +549,13 @@ def test_conv_tiles64(ops, case):
 
 # rows, K, N: one partial K chunk, the edges of the 2 / 4 / 8-wave splits (K 64,
 # 72, 248, 256), a chunk count that is no multiple of the waves, ragged 16x16
-# tiles; the last two take 32x32 tiles (over 1024 tiles of 16x16).
+# tiles; two cases take 32x32 tiles (over 1024 tiles of 16x16); the rest 64x64 ones
+# through LDS (256 of them and more) at the same edges of K, one with an odd
+# width; at 16 columns the small tiles again.
 F32_LINEAR_CASES = [(1, 8, 4), (17, 64, 16), (33, 72, 20), (40, 248, 36), (16, 256, 64), (5, 1032, 12),
-                    (4113, 40, 68), (8200, 264, 40)]
+                    (4113, 40, 68), (8200, 264, 40),
+                    (16321, 8, 20), (16390, 64, 33), (16385, 72, 36), (8200, 248, 100), (4100, 256, 196),
+                    (5470, 1032, 132), (16385, 264, 16)]
 
 
 @pytest.mark.parametrize("case", F32_LINEAR_CASES)
@@ -571,6 +575,39 @@ def test_linear_f32(ops, case):
     assert np.array_equal(full[:k], run(k))
     ref = x[0, 0].astype(np.float64) @ w.astype(np.float64).T + b + r[0, 0]
     assert rel_l2(full, ref) <= TOL["f32"]
+
+
+# n, H, W, c0, c1, cout, stride, up, affine: 256 tiles of 64x64 and more for the
+# batch, fewer for its first image (the small tiles).
+F32_TILED_CASES = [(17, 31, 33, 16, 8, 40, 1, 0, False), (17, 31, 33, 24, 0, 40, 1, 0, True),
+                   (18, 64, 60, 8, 0, 36, 2, 0, False), (9, 20, 24, 24, 0, 70, 1, 1, True)]
+
+
+@pytest.mark.parametrize("case", F32_TILED_CASES)
+def test_conv_f32_tiled(ops, case):
+    """The fp32 GEMM's 64x64 tiles: every loader option gives the first image
+    the bits it has alone and the last one the oracle's values."""
+    n, H, W, c0, c1, cout, stride, up, aff = case
+    rng = np.random.default_rng(hash(case) % 2**32)
+    x0 = _vals(rng, (n, H, W, c0), "f32")
+    x1 = _vals(rng, (n, H, W, c1), "f32") if c1 else None
+    w = _vals(rng, (cout, c0 + c1, 3, 3), "f32", 1.0 / math.sqrt(9 * (c0 + c1)))
+    b = rng.standard_normal(cout).astype(np.float32)
+    sc, sh = (1 + 0.3 * rng.standard_normal((n, c0 + c1))).astype(np.float32), _vals(rng, (n, c0 + c1), "f32")
+    wp, bd = _dev(_pack(w)), _dev(b)
+
+    def run(k):
+        return ops.conv(_dev(x0[:k]), wp, cout, 3, stride, up, x1=_dev(x1[:k]) if c1 else None,
+                        scale=_dev(sc[:k]) if aff else None, shift=_dev(sh[:k]) if aff else None, silu=int(aff),
+                        bias=bd).cpu().numpy()
+
+    full = run(n)
+    assert np.array_equal(full[:1], run(1))
+    a = (x0[-1] if not c1 else np.concatenate([x0[-1], x1[-1]], axis=2)).astype(np.float64)
+    if aff:
+        a = O.silu(a * sc[-1] + sh[-1])
+    ref = O.conv2d(O.upsample_nearest2x(a) if up else a, w, b, stride)
+    assert rel_l2(full[-1], ref) <= TOL["f32"]
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f32"])

@@ -74,6 +74,12 @@ def test_tiny_f32_30px_step(weights_cache):
     check("t_tiny_f32_30", weights_cache)
 
 
+def test_tiny_f32_72px_step(weights_cache):
+    """The fp32 GEMM's 64x64 tiles (five rows of 64x72 make 360 of them), the
+    residual blocks' conv + skip layers of two segments among them."""
+    check("t_tiny_f32_72", weights_cache, only=(1,))
+
+
 def test_tiny_bf16_step(weights_cache):
     check("t_tiny_bf16", weights_cache)
 
