@@ -1547,6 +1547,23 @@ static bool launch_tile64(const GemmArgs& a, hipStream_t s) {
   if (a.epi.geglu && a.K <= 640 && (long)((a.M + 255) / 256) * (a.N / 160) >= 512 &&
       launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s))
     return true;
+  // Short-K 1x1 layers spend their time in loads, epilogue and stores, which two
+  // blocks per CU overlap (the 32-deep tile; a 1x1 layer has the same bits in
+  // either depth).  At N = 320 the 256x320 tile reads its rows once instead of
+  // twice, which with a residual outweighs that.  64-deep choice against these:
+  // 49152 x 960 x 320 79.4 and 74.4 us, 65536 x 320 x 320 without residual 37.0
+  // and 34.6 (with it 41.9 and 44.0), 131072 x 128 x 256 42.0 and 39.4; below
+  // the stated grids 24576 x 960 x 320 56.6 and 57.1, 65536 x 128 x 128 18.7 and
+  // 22.1; 131072 x 640 x 640 178 and 191.
+  if (a.seg[0].ks == 1 && (a.seg[1].K == 0 || a.seg[1].ks == 1) && !a.epi.geglu && a.ksplit == 1) {
+    const long rows = (a.M + 255) / 256;
+    if (a.N % 160 == 0 && a.K <= 320 &&
+        (a.N >= 640 ? rows * (a.N / 160) >= 384 : !a.epi.resid && rows * (a.N / 160) >= 512) &&
+        launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s))
+      return true;
+    if (a.N % 160 && a.K <= 256 && rows * (a.N / 128) >= 384 && launch_dma<256, 128, 4, 1, 32, 3, 2>(a, s))
+      return true;
+  }
   switch (pick_tile64(a.M, a.N, a.K, a.ksplit)) {
     case 0: return launch_dma<64, 64, 2, 2, 64, 4, 2>(a, s);
     case 1: return launch_dma<128, 64, 2, 2, 64, 3, 2>(a, s);

@@ -512,6 +512,10 @@ TILE64_CASES = [
     (1, 1, 33003, 192, 64, 320, 1, 1, 0),  # linear, concat sources
     (2, 3, 1, 64, 0, 64, 3, 1, 0),        # six rows
     (1, 1, 1, 64, 0, 64, 1, 1, 0),        # one row, one K stage
+    # 1x1 layers of few channels on large grids: the 32-deep tiles, two per CU
+    (1, 1, 24400, 192, 128, 640, 1, 1, 0),  # 384 blocks of 256x160, concat sources
+    (1, 1, 65300, 64, 0, 320, 1, 1, 0),   # 512 blocks of 256x160, no residual
+    (1, 1, 49100, 128, 128, 256, 1, 1, 0),  # 384 blocks of 256x128, concat sources
 ]
 
 
