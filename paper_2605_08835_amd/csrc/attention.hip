@@ -163,8 +163,11 @@ __device__ __forceinline__ void softmax_max(f32x16 (&s)[QG][2], f32x16 (&o)[QG][
 // max rides in column d of the QK^T product.  SF: d < DP, the row sum rides
 // in row d of the PV product.  V is stored transposed per image
 // ([channel][token], as the projection GEMM writes it), so a V^T tile is
-// staged with 16-byte loads and stores.
-template <int D16, bool QS, bool MF, bool SF, int NW, int QG>
+// staged with 16-byte loads and stores.  ROWS: the output leaves through LDS in
+// 16-byte pieces of whole rows, else in 8-byte pieces from the registers (two
+// kernels, as one with both epilogues ran its loop up to 7 % slower: d = 96, 4096
+// tokens 68.6 and 74.1 us).
+template <int D16, bool QS, bool MF, bool SF, int NW, int QG, bool ROWS>
 __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(AttnArgs a) {
   using namespace fa;
   static_assert(QS || !MF, "the max can ride in the product only with pre-scaled queries");
@@ -551,8 +554,6 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
   static_assert(NW * 32 * LDK <= 2 * KT * LDK, "the waves' rows fit the K tiles");
   bf16* R = &Ks[0][0] + wave * 32 * LDK;
   bf16* O = reinterpret_cast<bf16*>(a.o) + (long)img * a.o_img + hd;
-  const bool rows16 =
-      a.Nq > DIRECT_NQ && (((uint64_t)a.o | (uint64_t)(2 * a.o_ld) | (uint64_t)(2 * a.o_img)) & 15) == 0;
   auto inv_sum = [&](int g) __attribute__((always_inline)) {
     float l = l_run[g];
     if constexpr (SF) {  // the ones row d of V^T accumulated the row sum into O^T row d
@@ -579,7 +580,7 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
         }
       }
   };
-  if (!rows16) {
+  if constexpr (!ROWS) {
 #pragma unroll
     for (int g = 0; g < QG; ++g) {
       const int q = qb + 32 * g + lq;
@@ -730,7 +731,6 @@ __global__ __launch_bounds__(256) void attn_f32_lanes_kernel(AttnArgs a) {
   }
 }
 
-// fp32, wider heads, and a single key (nothing to share out): one thread per query.
 template <int DMAX>
 static void launch_f32_lanes(const AttnArgs& a, hipStream_t s) {
   if (a.Nk <= 32)
@@ -739,6 +739,7 @@ static void launch_f32_lanes(const AttnArgs& a, hipStream_t s) {
     attn_f32_lanes_kernel<DMAX, 16><<<dim3((a.Nq + 15) / 16, a.heads, a.imgs), 256, 0, s>>>(a);
 }
 
+// fp32, wider heads, and a single key (nothing to share out): one thread per query.
 template <int DMAX, int KTF>
 __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
   __shared__ float Ks[KTF * DMAX];
@@ -798,7 +799,10 @@ static void launch_d(const AttnArgs& a, hipStream_t s) {
   // fragment reads per query, still two waves per SIMD); wider ones one.
   constexpr int NW = 4, QG = D16 <= 64 ? 2 : 1;
   dim3 grid((a.Nq + 32 * NW * QG - 1) / (32 * NW * QG), a.heads, a.imgs);
-  attn_bf16_kernel<D16, QS, MF, SF, NW, QG><<<grid, 64 * NW, 0, s>>>(a);
+  if (a.Nq > fa::DIRECT_NQ && (((uint64_t)a.o | (uint64_t)(2 * a.o_ld) | (uint64_t)(2 * a.o_img)) & 15) == 0)
+    attn_bf16_kernel<D16, QS, MF, SF, NW, QG, true><<<grid, 64 * NW, 0, s>>>(a);
+  else
+    attn_bf16_kernel<D16, QS, MF, SF, NW, QG, false><<<grid, 64 * NW, 0, s>>>(a);
 }
 
 // Head widths d (multiples of 8) whose 16-rounding is D16: d = D16 - 8
