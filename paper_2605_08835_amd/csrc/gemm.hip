@@ -49,28 +49,6 @@ __device__ inline const T* a_chunk_ptr(const ASeg& s, const RowPos& r, int tap, 
   return reinterpret_cast<const T*>(s.src1) + pix * s.c1 + (c - s.c0);
 }
 
-// 8 transformed A elements as floats (zero in the padding / past K).
-template <typename T>
-__device__ inline void a_chunk(const ASeg& s, const RowPos& r, int tap, int c, float v[8]) {
-  const T* p = a_chunk_ptr<T>(s, r, tap, c);
-  if (!p) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = 0.f;
-    return;
-  }
-  load8f(p, v);
-  if (s.scale) {
-    float sc[8], sh[8];
-    load8f(s.scale + (long)r.img * s.cin + c, sc);
-    load8f(s.shift + (long)r.img * s.cin + c, sh);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      v[i] = v[i] * sc[i] + sh[i];
-      if (s.silu) v[i] = silu_f(v[i]);
-    }
-  }
-}
-
 // bf16 chunk: raw 16-byte copy when no transform applies.
 __device__ inline bf16x8 a_chunk_bf16(const ASeg& s, const RowPos& r, int tap, int c) {
   bf16x8 z = {};
@@ -651,7 +629,7 @@ __device__ __forceinline__ int swz(int r) {
 }
 
 // Position of the operand loads in the K tiles, all wave-uniform.  Tiles come
-// in runs: with TI (images larger than 8x8) a run is one 32-channel block
+// in runs: with TI (images larger than 8x8) a run is one DK-channel block
 // under all taps of its layer, otherwise one tap (or 1x1 layer) over the
 // channels of one source.  Inside a run a tile only adds constants to the
 // source pointer, the weight offset and the tap number, so the refill beside
@@ -885,7 +863,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
     if (--s.left == 0) {
       next_run();
     } else {
-      const bool w = (s.wm >> s.tp) & 1;
+      const bool w = (s.wm >> (s.tp & 31)) & 1;  // (wm is 0 in the runs of more than 9 tiles)
       s.ab += pick(w, s.daw, s.da);
       s.sh -= pick(w, s.dshw, s.dsh);
       s.boff += s.db;
@@ -1609,18 +1587,17 @@ hipError_t launch_gemm(DType dt, const GemmArgs& args, hipStream_t s) {
     } else if (a.N % 160 == 0) {
       // 32-deep stages: 256x160 tiles, three of them (2 x 80.9 KB of LDS: two
       // blocks per CU); otherwise register-staged 64-deep tiles, one block per CU
-      const bool big = nblk(256, 160) * a.ksplit >= want;
       if (a.ksplit == 1 && nblk(256, 160) < 256 && launch_dma<64, 160, 2, 1, 32, 2, 4>(a, s)) {
         // short M: 64-row tiles, four blocks per CU
       } else if (launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s)) {
-      } else if (big) {
-        launch_bf16<256, 160, 64, 4, 1>(a, s);
+      } else if (nblk(256, 160) >= want) {  // (mode 0: the direct-to-LDS tiles take every other layer of these widths)
+        gemm_bf16_kernel<256, 160, 64, 4, 1, 0, 1><<<dim3((unsigned)nblk(256, 160)), dim3(256), 0, s>>>(a);
       } else {
-        launch_bf16<128, 160, 64, 4, 1>(a, s);
+        gemm_bf16_kernel<128, 160, 64, 4, 1, 0, 1><<<dim3((unsigned)nblk(128, 160)), dim3(256), 0, s>>>(a);
       }
     } else if (a.N % 128 == 0 && a.ksplit == 1 && launch_dma<256, 128, 4, 1, 32, 3, 2>(a, s)) {
-      // widths that are multiples of 128 but not of 160, 32-deep stages (the
-      // VAE decoder's conv_in): 256x128 tiles, waves of 64x128
+      // widths that are multiples of 128 but not of 160, channels of 32 but not
+      // of 64: 256x128 tiles, waves of 64x128
     } else if (a.N % 128 == 0 || a.N > 64) {
       if (nblk(256, 128) >= want)
         launch_bf16<256, 128, 64, 2, 2>(a, s);
