@@ -68,7 +68,9 @@ sd_status synerdiff_op_upconv(int32_t dtype, const void* d_x, int32_t n, int32_t
  * q_log2 = 1: Q already holds q * scale * log2(e), as the step's bf16
  * projections write it (scale is then unused).  Constraints: d a multiple
  * of 8; bf16: d rounded up to 16 is 16..96, 128, 160, 192 or 256; fp32:
- * d <= 256 (V row-major). */
+ * d <= 256 (V row-major).  bf16 reads Q and K in 16-byte and writes O in
+ * 8-byte pieces: start their rows at multiples of those (O rows at multiples
+ * of 16 bytes leave in 16-byte pieces). */
 sd_status synerdiff_op_attention(int32_t dtype, const void* d_q, int64_t q_ld, int64_t q_img,
                                  const void* d_k, int64_t k_ld, int64_t k_img, const void* d_v,
                                  int64_t v_ld, int64_t v_img, int32_t v_transposed,

@@ -447,7 +447,7 @@ __global__ __launch_bounds__(64 * NW, D16 <= 128 ? 2 : 1) void attn_bf16_kernel(
     // key 16u + 8(i/4) + 4 lh + i%4, i.e. register 8(u%2) + i of S^T tile u/2.
     // The steps (slice, group) run one behind the exp2s, so the products of a
     // step and the probabilities of the next can issue side by side (2 rows,
-    // 4096 tokens, d = 40: 77 -> 70 us; 12 rows 336 -> 332 us, where the
+    // 4096 tokens, d = 40: 75 -> 70 us; 12 rows 340 -> 333 us, where the
     // exp2s, a quarter of the plain rate, take most of the vector units' time).
     constexpr int NS = 2 * NKT * QG;  // steps: slice u = step / QG, group step % QG
     bf16x8 pf[2], vf[2][ND];

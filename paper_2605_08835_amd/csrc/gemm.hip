@@ -609,15 +609,17 @@ __global__ __launch_bounds__(256, MINB) void gemm_bf16_kernel(GemmArgs a) {
 // consecutive rows on distinct banks.  Lane l of a load writes (row
 // (64 / CPR) i + l / CPR, slot l % CPR) and fetches the chunk of that slot.
 //
-// What bounds these kernels is the operand stream: without the loads the
-// products with their LDS reads run at 1500-1900 TFLOP/s, the loads alone take
-// 75-95 % of the kernel's time.  A row of 64 bytes (DK = 32) moves a whole
-// 128-byte line from L2 for half of it: 66 B/ns per CU against 130 for rows of
-// 128 bytes (DK = 64; a loop of such loads over 2.6 MB).  So every layer whose
-// channels are multiples of 64 takes 64-deep stages; DKS-deep ones serve the
-// rest (conv_in, padded to 32 channels).  Against 32-deep stages with the
-// addresses formed per tile: 196608 x 320 x 2880 458 -> 323 us, 12288 x 1280 x
-// 11520 (2 splits) 364 -> 331 us, 512 x 1280 x 5120 100 -> 25 us.
+// No one unit bounds these kernels: at 196608 x 320 x 2880 the products with their
+// LDS reads take 241 us without the loads, the loads 210 us without the products,
+// both together 341 (12288 x 1280 x 11520 in 2 splits 235, 208 and 344; 24576 x
+// 640 x 2560 69, 64 and 90): the two streams overlap by a quarter to a third.
+// A row of 64 bytes (DK = 32) moves a whole 128-byte line from L2 for half of it:
+// 66 B/ns per CU against 130 for rows of 128 bytes (DK = 64; a loop of such loads
+// over 2.6 MB).  So every layer whose channels are multiples of 64 takes 64-deep
+// stages; DKS-deep ones serve the rest (conv_in, padded to 32 channels) and short
+// 1x1 layers.  Against 32-deep stages with the addresses formed per tile, in one
+// process: 196608 x 320 x 2880 389 -> 318 us, 12288 x 1280 x 11520 (2 splits) 359
+// -> 318 us, 512 x 1280 x 5120 100 -> 25 us.
 constexpr int DKS = 32;  // the smallest stage depth (the granule of split K and of the loader modes)
 
 // Slot swizzle of a tile row's 16-byte chunks: the fragment reads of rows
@@ -1478,10 +1480,14 @@ int gemm_ksplit(const GemmArgs& a) {
 
 // Tiles of the 64-deep direct-to-LDS kernel.  A block's time is modelled as
 // eb + nk * t us for its nk K tiles, t1 for a block alone on its CU and tf
-// when occ blocks share it (fitted to 149 conv and linear shapes of 64 to
-// 262144 rows; the modelled choice is within 2 % of the best tile on average,
-// 15 % at worst).  The tile never changes a row's K order, so every tile gives
-// the same bits and the choice may follow the row count.
+// when occ blocks share it, fitted to conv and linear shapes of 64 to 262144 rows.
+// For the tiles of one block per CU (occ 1) t1 stands for a grid or last round of
+// less than 256 blocks and tf for a full chip; what a full one adds is shared by
+// all CUs, and sets in late: 192 blocks of 256 x 320 measure 1.5 to 1.6 us a tile
+// (24576 x 640 x 2560 84 us, modelled 73).  A time in proportion to the filled share
+// was tried instead: of 761 shapes 46 moved by over 3 %, between -11 and +15 %, and
+// by +1.4 % in the mean, so the two values stay.  The tile never changes a row's
+// K order, so every tile gives the same bits and the choice may follow the row count.
 struct Tile64 {
   int bm, bn, occ;
   float t1, tf, eb;

@@ -77,8 +77,8 @@ CONV_CASES = [
     (3, 16, 16, 320, 320, 320, 3, 1, 0, False),
     (2, 24, 40, 96, 64, 160, 3, 1, 0, False),
     (1, 17, 9, 32, 0, 160, 3, 1, 0, False),
-    # widths that are multiples of 128 but not of 160 (the VAE decoder's): the
-    # 256x128 direct-to-LDS tiles (ragged, concat, upsampling, 1x1, many rows)
+    # widths that are multiples of 128 but not of 160 (the VAE decoder's): 64x64
+    # and, for the last, 128x128 direct-to-LDS tiles (ragged, concat, upsampling, 1x1)
     (2, 12, 12, 128, 0, 128, 3, 1, 0, False),
     (3, 9, 10, 256, 0, 256, 3, 1, 0, False),
     (2, 6, 6, 512, 0, 256, 3, 1, 1, False),
@@ -455,24 +455,25 @@ def test_conv_large_grid_rows_independent(ops):
 
 
 WIDE_CASES = [
-    # n, H, W, c0, c1, cout, resid, split.  Every case routes the whole batch to
-    # the 256x256 tiles (width % 256, K >= 2560, at least 128 blocks x splits,
-    # uniform-tap loader) and its first three images alone to the 256x160 or
-    # 256x128 tiles (too few blocks).
-    (40, 16, 16, 1280, 0, 1280, True, True),    # split in 2 (16x16 images), 400 blocks
-    (40, 16, 16, 1280, 0, 1280, True, False),   # one pass, 200 blocks
-    (130, 8, 8, 640, 0, 1280, True, True),      # 8x8 images: tap-outer K order, split in 4
-    (113, 12, 12, 1280, 0, 512, False, True),   # ragged last row tile (16272 rows), no split
-    (35, 31, 31, 160, 160, 256, True, True),    # concat sources, K = 2880, ragged (33635 rows)
-    (90, 12, 12, 1280, 0, 1280, True, True),    # split in 2 with a ragged last row tile (12960 rows)
+    # n, H, W, c0, c1, cout, resid, split.  The whole batch takes the wide tile
+    # named, its first three images alone the 64x64 or 128x64 one.
+    (40, 16, 16, 1280, 0, 1280, True, True),    # 256x256, split in 2 (16x16 images), 400 blocks
+    (40, 16, 16, 1280, 0, 1280, True, False),   # 256x256, one pass, 200 blocks
+    (130, 8, 8, 640, 0, 1280, True, True),      # 256x256, 8x8 images: tap-outer K order, split in 4
+    (113, 12, 12, 1280, 0, 512, False, True),   # 128x128, ragged last row tile (16272 rows), no split
+    (35, 31, 31, 128, 192, 256, True, True),    # 256x256, concat sources, K = 2880, ragged (33635 rows)
+    (90, 12, 12, 1280, 0, 1280, True, True),    # 256x256, split in 2 with a ragged last row tile (12960 rows)
+    # source widths that are no multiples of 64: the 32-deep 256x128 tile for the
+    # batch and the three images alike (here only the oracle checks it)
+    (35, 31, 31, 160, 160, 256, True, True),
 ]
 
 
 @pytest.mark.parametrize("case", WIDE_CASES)
 def test_conv_wide_tiles(ops, case):
-    """The 256x256 tiles (four 128x128 waves, AGPR accumulators) give every
-    image the same bits as the narrower tiles (its first images run alone on
-    those) and match the oracle on the first and last image."""
+    """The wide tiles on long K give every image the same bits as the narrow
+    ones (its first images run alone on those) and match the oracle on the first
+    and last image."""
     n, H, W, c0, c1, cout, with_resid, split = case
     log(f"wide tiles {case}")
     rng = np.random.default_rng(hash(case) % 2**32)
@@ -507,7 +508,9 @@ TILE64_CASES = [
     (33, 33, 31, 128, 64, 256, 3, 1, 0),  # 256x256 (33759 rows), concat sources
     (9, 61, 61, 64, 0, 320, 3, 1, 0),     # 256x320 (33489 rows)
     (130, 8, 8, 64, 128, 1280, 3, 1, 0),  # 256x256 on 8x8 images (taps outer), concat sources
-    (33, 32, 32, 64, 0, 256, 3, 2, 0),    # stride 2
+    (33, 32, 32, 64, 0, 256, 3, 2, 0),    # 128x64, stride 2
+    (33, 66, 62, 64, 0, 256, 3, 2, 0),    # 256x256, stride 2 (33759 rows)
+    (33, 66, 62, 64, 0, 320, 3, 2, 0),    # 256x320, stride 2 (33759 rows)
     (9, 30, 31, 64, 0, 320, 3, 1, 1),     # 256x320, upsampling
     (1, 1, 33003, 192, 64, 320, 1, 1, 0),  # linear, concat sources
     (2, 3, 1, 64, 0, 64, 3, 1, 0),        # six rows
