@@ -672,7 +672,13 @@ __device__ __forceinline__ T pick(bool c, T a, T b) {
 // and with them goes the refill of the stage this tile has freed.
 // UP: the layer upsamples its input (nearest 2x), so the input pixel of a tap
 // depends on the row's parity and is formed per tile.
-template <int BM, int BN, int WM, int WN, bool UP, int DK, int DNS, int MINB, bool TI>
+// LIN: a 1x1 layer of one source, so a row is its input pixel, no tap is masked
+// and the K tiles are one run.  The general form's setup costs a short layer
+// much, above all between other kernels, where its instructions come from beyond
+// the caches: 131072 x 320 x 320 in 256x160 tiles 69 us with the general setup and
+// 61 with this one (77 and 71 after four other kernels), 512 x 1280 x 1280 18.2 and
+// 15.8 (13.8 and 11.6), 49152 x 5120 x 640 451 and 424.
+template <int BM, int BN, int WM, int WN, bool UP, int DK, int DNS, int MINB, bool TI, bool LIN = false>
 __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmArgs a) {
   constexpr int NWV = WM * WN;                          // waves per block
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -720,6 +726,10 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
 #pragma unroll
   for (int j = 0; j < AW; ++j) {
     const int m = m0 + RPL * (wave * AW + j) + lrow;
+    if constexpr (LIN) {
+      pix[j] = m;
+      continue;
+    }
     const int img = m / hwo, p = m - img * hwo, oy = p / Wo, ox = p - oy * Wo;
     int mk = 0;
 #pragma unroll
@@ -756,7 +766,10 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
     s.cs2 = cs2;
     if constexpr (!UP) {
 #pragma unroll
-      for (int j = 0; j < AW; ++j) voffA[j] = pix[j] * cs2 + chunk16(wave * AW + j);
+      for (int j = 0; j < AW; ++j) {
+        voffA[j] = pix[j] * cs2 + chunk16(wave * AW + j);
+        if (LIN && pix[j] >= a.M) voffA[j] = OOB;
+      }
     }
   };
   // Start the run that holds (segment, tap, channel).
@@ -850,7 +863,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
         const int iy = ((pyx[j] >> 16) + ky) >> 1, ix = ((pyx[j] & 0xFFFF) + kx) >> 1;
         v = (pix[j] + iy * Wi + ix) * s.cs2 + chunk16(wave * AW + j);
       }
-      dma16(ares, adst + j * 512, ((nmask[j] << s.sh) & OOB) | (UP ? v & 0x7FFFFFFF : v), 0);
+      dma16(ares, adst + j * 512, LIN ? v | s.dead : ((nmask[j] << s.sh) & OOB) | (UP ? v & 0x7FFFFFFF : v), 0);
     }
     bf16* bdst = Bs + stg * BN * DK;
     const int boff = uni(s.boff);
@@ -861,6 +874,12 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
     }
   };
   auto advance = [&]() __attribute__((always_inline)) {
+    if constexpr (LIN) {
+      s.ab += 2 * DK;
+      s.boff += 2 * DK;
+      if (--s.togo <= 0) s.dead = OOB;
+      return;
+    }
     --s.togo;
     if (--s.left == 0) {
       next_run();
@@ -884,7 +903,11 @@ __global__ __launch_bounds__(64 * WM * WN, MINB) void gemm_bf16_dma_kernel(GemmA
   s.cs2 = -1;
   s.dead = 0;
   s.togo = nk;
-  if (nk > 0) {  // the run at K tile kb
+  if constexpr (LIN) {  // (never split)
+    s.ab = uni((const char*)g0s0);
+    s.boff = 0;
+    set_source(2 * g0c0);
+  } else if (nk > 0) {  // the run at K tile kb
     int kk = kb * DK, seg = 0;
     if (kk >= g0K) {
       seg = 1;
@@ -1449,7 +1472,9 @@ static bool launch_dma(const GemmArgs& a, hipStream_t s) {
   // K order (see the kernel): channel block outer, taps inner on images
   // larger than 8x8.
   const bool ti = (long)a.seg[0].Ho * a.seg[0].Wo > 64, up = a.seg[0].up != 0;
-  if (!up && ti)
+  if (a.seg[0].ks == 1 && a.seg[0].c1 == 0 && a.seg[1].K == 0 && a.ksplit == 1)  // (mode 1: stride 1, no upsampling)
+    gemm_bf16_dma_kernel<BM, BN, WM, WN, false, DK, DNS, MINB, false, true><<<g, b, 0, s>>>(a);
+  else if (!up && ti)
     gemm_bf16_dma_kernel<BM, BN, WM, WN, false, DK, DNS, MINB, true><<<g, b, 0, s>>>(a);
   else if (!up)
     gemm_bf16_dma_kernel<BM, BN, WM, WN, false, DK, DNS, MINB, false><<<g, b, 0, s>>>(a);
@@ -1531,23 +1556,17 @@ static bool launch_tile64(const GemmArgs& a, hipStream_t s) {
   if (a.epi.geglu && a.K <= 640 && (long)((a.M + 255) / 256) * (a.N / 160) >= 512 &&
       launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s))
     return true;
-  // Short-K 1x1 layers spend their time in loads, epilogue and stores, which two
-  // blocks per CU overlap (the 32-deep tile; a 1x1 layer has the same bits in
-  // either depth).  At N = 320 the 256x320 tile reads its rows once instead of
-  // twice, which with a residual outweighs that.  64-deep choice against these:
-  // 49152 x 960 x 320 79.4 and 74.4 us, 65536 x 320 x 320 without residual 37.0
-  // and 34.6 (with it 41.9 and 44.0), 131072 x 128 x 256 42.0 and 39.4; below
-  // the stated grids 24576 x 960 x 320 56.6 and 57.1, 65536 x 128 x 128 18.7 and
-  // 22.1; 131072 x 640 x 640 178 and 191.
-  if (a.seg[0].ks == 1 && (a.seg[1].K == 0 || a.seg[1].ks == 1) && !a.epi.geglu && a.ksplit == 1) {
-    const long rows = (a.M + 255) / 256;
-    if (a.N % 160 == 0 && a.K <= 320 &&
-        (a.N >= 640 ? rows * (a.N / 160) >= 384 : !a.epi.resid && rows * (a.N / 160) >= 512) &&
-        launch_dma<256, 160, 4, 1, 32, 3, 2>(a, s))
-      return true;
-    if (a.N % 160 && a.K <= 256 && rows * (a.N / 128) >= 384 && launch_dma<256, 128, 4, 1, 32, 3, 2>(a, s))
-      return true;
-  }
+  // Short-K 1x1 layers of 128-column tiles spend their time in loads, epilogue and
+  // stores, which two blocks per CU overlap (the 32-deep tile; a 1x1 layer has the
+  // same bits in either depth): 64-deep choice and this one 98304 x 128 x 128 26.3
+  // and 24.0 us, 65536 x 256 x 256 34.0 and 30.5; below the stated grid 65536 x 128
+  // x 128 18.7 and 22.1, at K = 512 196608 x 512 x 512 equal.  (At the widths that
+  // are multiples of 160 it depends on the surroundings: 49152 x 960 x 320 alone
+  // 80.7 and 70.6, but in the 48-row step the 196608-row QKV 216 and 222, the query
+  // projection 81 and 88.)
+  if (a.seg[0].ks == 1 && (a.seg[1].K == 0 || a.seg[1].ks == 1) && !a.epi.geglu && a.ksplit == 1 && a.N % 160 &&
+      a.K <= 256 && (long)((a.M + 255) / 256) * (a.N / 128) >= 384 && launch_dma<256, 128, 4, 1, 32, 3, 2>(a, s))
+    return true;
   switch (pick_tile64(a.M, a.N, a.K, a.ksplit)) {
     case 0: return launch_dma<64, 64, 2, 2, 64, 4, 2>(a, s);
     case 1: return launch_dma<128, 64, 2, 2, 64, 3, 2>(a, s);

@@ -515,10 +515,17 @@ TILE64_CASES = [
     (1, 1, 33003, 192, 64, 320, 1, 1, 0),  # linear, concat sources
     (2, 3, 1, 64, 0, 64, 3, 1, 0),        # six rows
     (1, 1, 1, 64, 0, 64, 1, 1, 0),        # one row, one K stage
-    # 1x1 layers of few channels on large grids: the 32-deep tiles, two per CU
-    (1, 1, 24400, 192, 128, 640, 1, 1, 0),  # 384 blocks of 256x160, concat sources
-    (1, 1, 65300, 64, 0, 320, 1, 1, 0),   # 512 blocks of 256x160, no residual
-    (1, 1, 49100, 128, 128, 256, 1, 1, 0),  # 384 blocks of 256x128, concat sources
+    (1, 1, 49100, 128, 128, 256, 1, 1, 0),  # few channels, 384 blocks: 32-deep 256x128, concat sources
+    # linear layers of one source, which have a setup of their own, on every tile
+    (1, 1, 49100, 192, 0, 256, 1, 1, 0),   # 32-deep 256x128, two per CU
+    (1, 1, 33231, 128, 0, 64, 1, 1, 0),    # 128x64
+    (1, 1, 33299, 128, 0, 128, 1, 1, 0),   # 128x128
+    (1, 1, 20435, 64, 0, 160, 1, 1, 0),    # 128x160
+    (1, 1, 33759, 320, 0, 256, 1, 1, 0),   # 256x256
+    (1, 1, 65300, 64, 0, 320, 1, 1, 0),    # 256x320
+    (1, 1, 301, 96, 0, 160, 1, 1, 0),      # 32-deep 64x160
+    (1, 1, 65600, 32, 0, 160, 1, 1, 0),    # 32-deep 256x160, one K tile
+    (1, 1, 7001, 1056, 0, 256, 1, 1, 0),   # 32-deep 256x128
 ]
 
 
